@@ -80,6 +80,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wide_kernel(const bf16_t *__r
     const uint2 *xl8 = reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(Xv) + act24_lo_base(KT)) + lane;     // 1-byte lo plane (P3)
     const size_t ztile = (size_t)SJD_MTILES * KT;        // the all-zero tile behind every activation matrix
     const bf16x8 *zw = xp + ztile * 64;
+    if ((int)blockIdx.x * NW * G >= groups) return;      // (a column group added by rounding the grid up)
     // this wave's packed weight groups (a group past the end reads the zero tile and stores nothing)
     const bf16x8 *wp[G];
     int grp[G];
@@ -226,43 +227,57 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wide_kernel(const bf16_t *__r
 // Second kernel: adds the K-slices of every accumulator fragment in slice order, applies
 // rsqrt(mean(x^2) + eps) of each token when an RMSNorm is folded into the projection (PRO_NORM: the
 // planes held x * gain and ssq_in the per-16-feature sums of squares of x), and runs the epilogue.
-// Workgroup (x, mt): M-tile mt, EPI_TILES consecutive n tiles; lane l of a wave holds features
-// 16 ntile + 4 (l / 16) .. + 4 of token 16 mt + l % 16, exactly as the MFMA left them.
-#define EPI_TILES 8
+// Workgroup (x, mt): M-tile mt, the `ft` n tiles of column group x, one per wave; lane l of a wave holds features
+// 16 ntile + 4 (l / 16) .. + 4 of token 16 mt + l % 16, exactly as the MFMA left them.  What it costs is latency: a
+// launch, one round of loads, the stores.  So everything (up to four slices, the epilogue's operands, the sums of
+// squares) is requested before anything is used, and the workgroups are cut like those of the first kernel: with both
+// grids a multiple of eight column groups wide, a group's slices and its epilogue meet in one XCD's L2.
 template <int EPI, int PRO>
-__global__ __launch_bounds__(256) void gemm_wide_epilogue_kernel(const f32x4 *__restrict__ part, int KS, int MT, int NT,
+__global__ __launch_bounds__(1024) void gemm_wide_epilogue_kernel(const f32x4 *__restrict__ part, int KS, int MT, int NT,
                                                                  const float *__restrict__ ssq_in, float eps, int N, int K,
                                                                  SjdGemmEpi ep)
 {
     __shared__ float rs[16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
-    const int mt = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, c = lane & 15;
+    const int ft = blockDim.x >> 6, mt = blockIdx.y;
+    if ((int)blockIdx.x * ft >= NT) return;                                    // (a column group added by rounding up)
+    const int nt = blockIdx.x * ft + wave, ntile = min(nt, NT - 1);            // (past the end: the last tile, not written)
+    const f32x4 *p = part + ((size_t)mt * NT + ntile) * 64 + lane;
+    const size_t step = (size_t)MT * NT * 64;                     // from one slice to the next
+    f32x4 q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = p[(size_t)min(i, KS - 1) * step];
+    const int f_m = mt * 16 + c, f_n0 = ntile * 16 + g * 4;
+    EpiPre pre;
+    preload_epilogue<EPI>(ep, N, f_m, f_n0, pre);
     if (PRO == SJD_PRO_NORM) {
+      if (threadIdx.x < 256) {
         // 16 threads per token add every 16th float4 of its row of partial sums, then fold
         const int tok = threadIdx.x >> 4, sl = threadIdx.x & 15;
         const int NQ = ssq_stride(K) / 4;
         const f32x4 *pp = reinterpret_cast<const f32x4 *>(ssq_in + (size_t)(mt * 16 + tok) * (NQ * 4));
         float t = 0.f;
+#pragma unroll 4
         for (int i = sl; i < NQ; i += 16) { const f32x4 v = pp[i]; t += (v[0] + v[1]) + (v[2] + v[3]); }
         t += __shfl_xor(t, 8);
         t += __shfl_xor(t, 4);
         t += __shfl_xor(t, 2);
         t += __shfl_xor(t, 1);
         if (sl == 0) rs[tok] = rsqrtf(t / (float)K + eps);
-        __syncthreads();
+      }
+      __syncthreads();
     }
-    const float scale = PRO == SJD_PRO_NORM ? rs[c] : 1.0f;
-    for (int i = wave; i < EPI_TILES; i += 4) {
-        const int ntile = blockIdx.x * EPI_TILES + i;
-        if (ntile >= NT) break;
-        const int f_m = mt * 16 + c, f_n0 = ntile * 16 + g * 4;
-        EpiPre pre;
-        preload_epilogue<EPI>(ep, N, f_m, f_n0, pre);
-        f32x4 v = part[((size_t)mt * NT + ntile) * 64 + lane];
-        for (int y = 1; y < KS; ++y) v += part[(((size_t)y * MT + mt) * NT + ntile) * 64 + lane];
-        if (PRO == SJD_PRO_NORM) v *= scale;
-        apply_epilogue<EPI>(ep, N, f_m, f_n0, v, pre);
+    f32x4 v = q[0];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) if (i < KS) v += q[i];
+    for (int y = 4; y < KS; y += 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = p[(size_t)min(y + i, KS - 1) * step];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (y + i < KS) v += q[i];
     }
+    if (PRO == SJD_PRO_NORM) v *= rs[c];
+    if (nt < NT) apply_epilogue<EPI>(ep, N, f_m, f_n0, v, pre);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -301,6 +316,16 @@ int sjd_gemm_wide_setup()
     return SJD_OK;
 }
 
+// Column groups of both kernels' grids.  Workgroup i of a launch runs on XCD i % 8: with a multiple of eight column
+// groups the K-slices of a group and its epilogue share an L2, so the count is rounded up (the added workgroups return
+// at once) where all workgroups of the first kernel are resident together, one per CU (775M QKV at 128 rows, 36 groups:
+// 14.3 -> 13.1 us for the pair; 7B gate/up at 128 rows, 172 groups x 2 slices: 62.7 -> 69.4 us, so not there).
+static int wide_cols(int groups, int g, int ks)
+{
+    const int cols = (groups + WIDE_WAVES * g - 1) / (WIDE_WAVES * g), up = (cols + 7) & ~7;
+    return cols >= 32 && up * ks <= 256 ? up : cols;
+}
+
 template <int MT, int TN, int G>
 static int launch_wide_t(const SjdLinear *lin, const void *act, int ks, int kps, f32x4 *part, hipStream_t s)
 {
@@ -308,7 +333,7 @@ static int launch_wide_t(const SjdLinear *lin, const void *act, int ks, int kps,
     const size_t lds = (size_t)2 * KU * MT * 2 * 1024;
     SJD_TRY((enable_lds_t<MT, TN, G>()));
     const int groups = lin->N / 16 / TN;
-    dim3 grid((groups + WIDE_WAVES * G - 1) / (WIDE_WAVES * G), ks);
+    dim3 grid(wide_cols(groups, G, ks), ks);
     SJD_LAUNCH((gemm_wide_kernel<MT, TN, G, KU, WIDE_WAVES, false, false>), grid, dim3(64 * WIDE_WAVES), lds, s,
                (const bf16_t *)lin->w, act, lin->N, lin->K, kps, part, (const float *)nullptr, 0.f, SjdGemmEpi{});
     HIP_TRY(hipGetLastError());
@@ -400,8 +425,9 @@ int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq
     }
     SJD_TRY(rc);
     const int NT = lin->N / 16;
-    dim3 grid((NT + EPI_TILES - 1) / EPI_TILES, mt);
-#define GO(EPI, PRO) SJD_LAUNCH((gemm_wide_epilogue_kernel<EPI, PRO>), grid, dim3(256), 0, s, p4, ks, mt, NT, ssq_in, eps, lin->N, lin->K, ep)
+    dim3 grid(wide_cols(NT / lin->tn, g, ks), mt);
+    const dim3 block(64 * WIDE_WAVES * g * lin->tn);      // 256 .. 1024
+#define GO(EPI, PRO) SJD_LAUNCH((gemm_wide_epilogue_kernel<EPI, PRO>), grid, block, 0, s, p4, ks, mt, NT, ssq_in, eps, lin->N, lin->K, ep)
     if (ssq_in) {
         switch (ep.kind) {
             case SJD_EPI_STORE: GO(SJD_EPI_STORE, SJD_PRO_NORM); break;
