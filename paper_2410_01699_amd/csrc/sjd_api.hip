@@ -526,11 +526,11 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     return SJD_OK;
 }
 
-// Embedding + decoder stack for one window or prompt chunk of one handle.  ids (device) or emb_rows
-// (device fp32 rows), `rows` of them; stream_mode as in handle_streams.  Two streams see the same
+// Embedding + decoder stack for one window or prompt chunk of one handle: `rows` rows, the first id_rows of them
+// from ids (device), the others from emb_rows (device fp32 rows); stream_mode as in handle_streams.  Two streams see the same
 // rows; their logits land in rows 0.. and (1 << cfg_shift(rows)).. of `logits`.
-static int forward_window(sjd_model *m, sjd_kv *kv, const int32_t *ids, const float *emb_rows, int32_t rows,
-                          int32_t rows_valid, int32_t stream_mode, float *logits, hipStream_t s)
+static int forward_window(sjd_model *m, sjd_kv *kv, const int32_t *ids, int32_t id_rows, const float *emb_rows,
+                          int32_t rows, int32_t rows_valid, int32_t stream_mode, float *logits, hipStream_t s)
 {
     if (rows > rows_max(m) || (stream_mode == 2 && rows > rows_max(m) / 2)) return SJD_EINVAL;
     kv->last_stream = s;
@@ -539,7 +539,7 @@ static int forward_window(sjd_model *m, sjd_kv *kv, const int32_t *ids, const fl
         const int32_t *idv[SJD_MAX_STREAMS] = {ids, ids};
         int32_t *errv[SJD_MAX_STREAMS] = {&kv->state->err, &kv->state->err};
         const bool lo16 = rows_use_lo16(((sm.count - 1) << sm.shift) + rows);
-        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, idv, emb_rows, rows, sm, kv->x, kv->x24, kv->ssq, errv, lo16, s));
+        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, idv, id_rows, emb_rows, rows, sm, kv->x, kv->x24, kv->ssq, errv, lo16, s));
         // (only the profiler uses the count: it has read the true lengths before the iteration)
         const double toks = kv->prof ? kv->prof_kv_tokens
                                      : (stream_mode == 1 ? 0 : kv->n_upper + rows) + (stream_mode == 0 ? 0 : kv->n_upper_u + rows);
@@ -550,7 +550,7 @@ static int forward_window(sjd_model *m, sjd_kv *kv, const int32_t *ids, const fl
     const int32_t *idv[SJD_MAX_STREAMS] = {ids};
     int32_t *errv[SJD_MAX_STREAMS] = {&kv->state->err};
     for (int stream = (stream_mode == 1 ? 1 : 0); stream <= (stream_mode == 0 ? 0 : 1); ++stream) {
-        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, idv, emb_rows, rows, one, kv->x, kv->x24, kv->ssq, errv, false, s));
+        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, idv, id_rows, emb_rows, rows, one, kv->x, kv->x24, kv->ssq, errv, false, s));
         SJD_TRY(forward_rows_f32(m, kv, rows, rows_valid, stream,
                                  logits + (stream_mode == 2 && stream ? ((size_t)1 << cfg_shift(rows)) * m->V_s : 0), s));
     }
@@ -581,21 +581,22 @@ extern "C" int sjd_forward_logits(sjd_model *m, sjd_kv *kv, const int32_t *token
     hipStream_t s = (hipStream_t)stream;
     SJD_LAUNCH(clear_done_kernel, dim3(1), dim3(1), 0, s, kv->state);
     HIP_TRY(hipGetLastError());
-    if (!kv->cfg_on) return forward_window(m, kv, tokens, nullptr, L, L, 0, logits, s);
-    SJD_TRY(forward_window(m, kv, tokens, nullptr, L, L, 2, kv->logits, s));
+    if (!kv->cfg_on) return forward_window(m, kv, tokens, L, nullptr, L, L, 0, logits, s);
+    SJD_TRY(forward_window(m, kv, tokens, L, nullptr, L, L, 2, kv->logits, s));
     return sjd_launch_guide(kv->logits, kv->logits + ((size_t)1 << cfg_shift(L)) * m->V_s, kv->cfg_scale, (size_t)L * m->V_s,
                             logits, s);
 }
 
-// rows appended to stream `stream`; the ids of stream 0 are recorded for the repeat initialisers
-__global__ void advance_n_kernel(SjdState *st, int32_t *tokens, const int32_t *ids, int rows, int stream)
+// rows appended to stream `stream`; the ids of stream 0 are recorded for the repeat initialisers (-1: a raw
+// embedding row, from row id_rows on)
+__global__ void advance_n_kernel(SjdState *st, int32_t *tokens, const int32_t *ids, int id_rows, int rows, int stream)
 {
     if (stream) {
         if (threadIdx.x == 0) st->n_u += rows;
         return;
     }
     const int n = st->n;
-    for (int r = threadIdx.x; r < rows; r += blockDim.x) tokens[n + r] = ids ? ids[r] : -1;
+    for (int r = threadIdx.x; r < rows; r += blockDim.x) tokens[n + r] = r < id_rows ? ids[r] : -1;
     __syncthreads();
     if (threadIdx.x == 0) st->n = n + rows;
 }
@@ -606,7 +607,9 @@ __global__ void forced_first_kernel(int32_t *forced, sjd_init init, int lo)
 }
 
 // the prompt of one stream, in chunks of up to SJD_ROWS_MAX positions; leaves the raw logits of the
-// last position in kv->logits row *rows_last - 1
+// last position in kv->logits row *rows_last - 1.  A chunk may hold the last ids and the first embedding rows: one
+// forward, because a forward costs a pass over the weights however few rows it has (775M, 1 id + 120 rows: the
+// forward of the one id was 0.83 of 2.85 ms).
 static int prefill_stream(sjd_model *m, sjd_kv *kv, int32_t stream_id, const int32_t *ids, int32_t n_ids,
                           const float *embeds, int32_t n_embeds, int *rows_last, hipStream_t s)
 {
@@ -615,29 +618,18 @@ static int prefill_stream(sjd_model *m, sjd_kv *kv, int32_t stream_id, const int
     for (int p0 = 0; p0 < P; p0 += chunk) {
         const int rows = std::min(chunk, P - p0);
         const int id_rows = std::max(0, std::min(rows, n_ids - p0));   // leading rows that are ids
-        // a chunk is either all ids or all embedding rows; split mixed chunks
-        int done_rows = 0;
-        while (done_rows < rows) {
-            int cnt; bool is_id = (p0 + done_rows) < n_ids;
-            cnt = is_id ? (id_rows - done_rows) : (rows - done_rows);
-            if (is_id) {
-                HIP_TRY(hipMemcpyAsync(kv->ids_stage, ids + p0 + done_rows, (size_t)cnt * 4, hipMemcpyHostToDevice, s));
-                HIP_TRY(hipStreamSynchronize(s));
-                SJD_TRY(forward_window(m, kv, kv->ids_stage, nullptr, cnt, cnt, stream_id, kv->logits, s));
-            } else {
-                HIP_TRY(hipMemcpyAsync(kv->emb_stage, embeds + (size_t)(p0 + done_rows - n_ids) * d, (size_t)cnt * d * 4,
-                                       hipMemcpyHostToDevice, s));
-                HIP_TRY(hipStreamSynchronize(s));
-                SJD_TRY(forward_window(m, kv, nullptr, kv->emb_stage, cnt, cnt, stream_id, kv->logits, s));
-            }
-            SJD_LAUNCH(advance_n_kernel, dim3(1), dim3(64), 0, s, kv->state, kv->tokens,
-                               is_id ? kv->ids_stage : (const int32_t *)nullptr, cnt, stream_id);
-            HIP_TRY(hipGetLastError());
-            HIP_TRY(hipStreamSynchronize(s));   // staging buffers are reused by the next chunk
-            if (stream_id) kv->n_upper_u += cnt; else kv->n_upper += cnt;
-            done_rows += cnt;
-            *rows_last = cnt;
-        }
+        if (id_rows > 0)
+            HIP_TRY(hipMemcpyAsync(kv->ids_stage, ids + p0, (size_t)id_rows * 4, hipMemcpyHostToDevice, s));
+        if (id_rows < rows)
+            HIP_TRY(hipMemcpyAsync(kv->emb_stage, embeds + (size_t)(p0 + id_rows - n_ids) * d, (size_t)(rows - id_rows) * d * 4,
+                                   hipMemcpyHostToDevice, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        SJD_TRY(forward_window(m, kv, kv->ids_stage, id_rows, kv->emb_stage, rows, rows, stream_id, kv->logits, s));
+        SJD_LAUNCH(advance_n_kernel, dim3(1), dim3(64), 0, s, kv->state, kv->tokens, kv->ids_stage, id_rows, rows, stream_id);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(s));   // staging buffers are reused by the next chunk
+        if (stream_id) kv->n_upper_u += rows; else kv->n_upper += rows;
+        *rows_last = rows;
     }
     return SJD_OK;
 }
@@ -753,7 +745,7 @@ static int enqueue_step(sjd_model *m, sjd_kv *kv, const int32_t *draft, const fl
                         const sjd_sampler *smp, const sjd_init *init, uint64_t seed, int32_t *n_accepted,
                         int32_t *new_draft, float *p_new, hipStream_t s)
 {
-    SJD_TRY(forward_window(m, kv, draft, nullptr, L, L, kv->cfg_on ? 2 : 0, kv->logits, s));
+    SJD_TRY(forward_window(m, kv, draft, L, nullptr, L, L, kv->cfg_on ? 2 : 0, kv->logits, s));
     SjdVerifyArgs v;
     memset(&v, 0, sizeof(v));
     if (kv->cfg_on) { v.logits_u = kv->logits + ((size_t)1 << cfg_shift(L)) * m->V_s; v.cfg_scale = kv->cfg_scale; }
@@ -944,7 +936,7 @@ static int forward_batch(sjd_model *m, sjd_kv *const *kvs, int32_t B, const int3
         kvs[b]->last_stream = s;
     }
     const bool lo16 = rows_use_lo16(((sm.count - 1) << sm.shift) + L);
-    PROF(kv0, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, ids_s, nullptr, L, sm, kv0->x, kv0->x24, kv0->ssq, errv, lo16, s));
+    PROF(kv0, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, ids_s, L, nullptr, L, sm, kv0->x, kv0->x24, kv0->ssq, errv, lo16, s));
     double toks = 0;
     for (int b = 0; b < B; ++b) toks += kvs[b]->n_upper + L + (kv0->cfg_on ? kvs[b]->n_upper_u + L : 0);
     if (kv0->prof) toks = kv0->prof_kv_tokens;

@@ -332,12 +332,12 @@ struct sjd_kv {
 
 // ---- kernel launchers (each returns SJD_OK or an SJD_E* code) --------------------------------
 // `st` (device, fp32 models' kernels) lets a kernel skip its work once a generation has finished; NULL = always run.
-// bf16 models: `rows` rows per stream, stream s from ids[s] (device ids; all streams share emb_rows when
-// that is given instead), written at row s << sm.shift.  fp32 models: one stream, ids[0].
+// bf16 models: `rows` rows per stream, stream s from ids[s] (device ids; from row id_rows on all streams share
+// emb_rows), written at row s << sm.shift.  fp32 models: one stream, ids[0].
 // err[s] (device, may be NULL): receives SJD_DEVERR_TOKEN_ID when an id of stream s lies outside the vocabulary
 // lo16: x24 gets the 2-byte lo plane (the forward runs on the wide projection kernel)
-int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, const float *emb_rows, int32_t rows,
-                     const SjdStreams &sm, float *x, void *x24, float *ssq, int32_t *const *err, bool lo16, hipStream_t s);
+int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, int32_t id_rows, const float *emb_rows,
+                     int32_t rows, const SjdStreams &sm, float *x, void *x24, float *ssq, int32_t *const *err, bool lo16, hipStream_t s);
 int sjd_launch_rmsnorm(const sjd_model *m, float *x, const float *part, int32_t n_part, size_t part_stride,
                        const void *gain, int32_t rows, void *h, const SjdState *st, hipStream_t s);
 int sjd_launch_rope_kv(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t stream, const float *part, int32_t n_part,

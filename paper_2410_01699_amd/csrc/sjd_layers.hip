@@ -13,14 +13,14 @@ template <> struct Act<bf16_t> {
     __device__ static float load(const bf16_t *p, size_t i) { return bf16_to_f32(p[i]); }
 };
 
-// x[row][:] = E[id][:]  (or the given raw embedding row); bf16 models keep x in act_off order and leave
+// x[row][:] = E[id][:], from row `id_rows` on the given raw embedding rows (a prompt's ids lead); bf16 models keep x in act_off order and leave
 // what the first projection reads: the hi / lo planes of x * gain (first layer's attention norm) in
 // x24 and the sums of squares of x per 16 features in ssq.  Stream
 // blockIdx.z takes its ids from ids.p[stream] and writes rows (stream << shift)..; one thread per 4
 // consecutive features; grid (rows per stream, d / 1024, streams).
 struct EmbedIds { const int32_t *p[SJD_MAX_STREAMS]; int32_t *err[SJD_MAX_STREAMS]; };
 template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T *E, EmbedIds ids, const float *emb_rows, int d, int shift,
+__global__ __launch_bounds__(256) void embed_kernel(const T *E, EmbedIds ids, const float *emb_rows, int id_rows, int d, int shift,
                                                     float *x, void *x24, const bf16_t *gain, float *ssq, int vocab, int lo16)
 {
     const int stream = blockIdx.z;
@@ -30,12 +30,13 @@ __global__ __launch_bounds__(256) void embed_kernel(const T *E, EmbedIds ids, co
     float4 v;
     // an id outside the vocabulary (the ids come from caller-supplied device memory) reads nothing: its
     // row is zero and the error flag of the handle's state is raised
-    const int id = emb_rows ? 0 : ids.p[stream][r];
+    const bool raw = r >= id_rows;
+    const int id = raw ? 0 : ids.p[stream][r];
     if (id < 0 || id >= vocab) {
         v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (j == 0 && ids.err[stream]) *ids.err[stream] = SJD_DEVERR_TOKEN_ID;
-    } else if (emb_rows) {
-        v = *reinterpret_cast<const float4 *>(emb_rows + (size_t)r * d + j);
+    } else if (raw) {
+        v = *reinterpret_cast<const float4 *>(emb_rows + (size_t)(r - id_rows) * d + j);
     } else if (sizeof(T) == 2) {
         const uint2 u = *reinterpret_cast<const uint2 *>(reinterpret_cast<const bf16_t *>(E) + (size_t)id * d + j);
         v = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
@@ -155,12 +156,13 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float *part, int
 // ---------------------------------------------------------------------------------------------
 #define LAUNCH_CHECK() HIP_TRY(hipGetLastError())
 
-int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, const float *emb_rows, int32_t rows,
-                     const SjdStreams &sm, float *x, void *x24, float *ssq, int32_t *const *err, bool lo16, hipStream_t s)
+int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, int32_t id_rows, const float *emb_rows,
+                     int32_t rows, const SjdStreams &sm, float *x, void *x24, float *ssq, int32_t *const *err, bool lo16, hipStream_t s)
 {
     if (sm.count < 1 || sm.count > SJD_MAX_STREAMS || rows < 1 || rows > (1 << sm.shift) ||
         (sm.count << sm.shift) > SJD_ROWS_MAX)
         return SJD_EINVAL;
+    if (id_rows < 0 || id_rows > rows || (id_rows < rows && !emb_rows)) return SJD_EINVAL;
     if (m->cfg.dtype == 0 && sm.count != 1) return SJD_EINVAL;
     if (m->cfg.dtype == 1 && (!x24 || !ssq)) return SJD_EINVAL;
     const int d = m->cfg.d_model;
@@ -171,9 +173,9 @@ int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, const float 
     }
     const dim3 grid(rows, (d + 1023) / 1024, sm.count);
     if (m->cfg.dtype == 0)
-        SJD_LAUNCH(embed_kernel<float>, grid, dim3(256), 0, s, (const float *)m->E, e, emb_rows, d, sm.shift, x, x24, (const bf16_t *)nullptr, ssq, m->cfg.vocab_total, lo16 ? 1 : 0);
+        SJD_LAUNCH(embed_kernel<float>, grid, dim3(256), 0, s, (const float *)m->E, e, emb_rows, id_rows, d, sm.shift, x, x24, (const bf16_t *)nullptr, ssq, m->cfg.vocab_total, lo16 ? 1 : 0);
     else
-        SJD_LAUNCH(embed_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t *)m->E, e, emb_rows, d, sm.shift, x, x24, (const bf16_t *)m->layers[0].g1, ssq, m->cfg.vocab_total, lo16 ? 1 : 0);
+        SJD_LAUNCH(embed_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t *)m->E, e, emb_rows, id_rows, d, sm.shift, x, x24, (const bf16_t *)m->layers[0].g1, ssq, m->cfg.vocab_total, lo16 ? 1 : 0);
     LAUNCH_CHECK();
     return SJD_OK;
 }
