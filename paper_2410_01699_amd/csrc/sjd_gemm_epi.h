@@ -57,7 +57,7 @@ struct EpiPre {
     float c0, s0, c1, s1;     // QKV: RoPE factors of this thread's two pairs
     int pos;                  // QKV: absolute position of row m in its stream's cache
     int row;                  // QKV: row index inside the stream
-    bf16_t *cache;            // QKV: this layer of the stream's cache (NULL: the row belongs to no stream)
+    SJD_GLOBAL bf16_t *cache; // QKV: this layer of the stream's cache (NULL: the row belongs to no stream)
 };
 
 template <int EPI>
@@ -68,16 +68,35 @@ __device__ __forceinline__ void preload_epilogue(const SjdGemmEpi &ep, int N, in
         pre.gn = ep.out24 ? *reinterpret_cast<const uint2 *>(ep.gain_next + n0) : make_uint2(0u, 0u);
     } else if (EPI == SJD_EPI_QKV) {
         const int half = ep.hd >> 1;
-        // the stream that owns row m: its cache length and cache (the loop index is uniform, so the
-        // table reads are scalar loads; the selection is per lane)
+        // the stream that owns row m: its cache length and cache.  What this costs is round trips to memory in front of
+        // the stores, so it is two scalar loads in a row whatever the number of streams (walking the table entry by entry
+        // made the 775M forward of 4 images 1576 us, now 1565).
         const int stream = m >> ep.sm.shift;
         pre.row = m & ((1 << ep.sm.shift) - 1);
-        int n_s = ep.sm.count > 0 ? *ep.sm.first.n : 0;
-        pre.cache = (stream == 0 && ep.sm.count > 0) ? ep.sm.first.kvc + ep.layer_off : nullptr;
-        for (int s = 1; s < ep.sm.count; ++s) {            // uniform index: scalar table reads
-            const SjdStreamEntry e = ep.sm.table[s];
-            const int n_here = *e.n;
-            if (s == stream) { n_s = n_here; pre.cache = e.kvc + ep.layer_off; }
+        int n_s = 0;
+        pre.cache = nullptr;
+        if (ep.sm.shift >= 4) {
+            // a stream owns whole 16-row tiles: one owner per wave
+            const int su = __builtin_amdgcn_readfirstlane(stream);
+            if (su < ep.sm.count) {
+                const SjdStreamEntry e = stream_entry(ep.sm, su);
+                n_s = *as_global(e.n);
+                pre.cache = as_global(e.kvc) + ep.layer_off;
+            }
+        } else {
+            // several owners in a tile: every entry, then every length, requested together; each lane picks its own
+            // (count > 1 here: a lone stream has all rows)
+            SjdStreamEntry e[SJD_MAX_STREAMS];
+            int n_e[SJD_MAX_STREAMS];
+            if (ep.sm.count > 0) {
+#pragma unroll
+                for (int i = 0; i < SJD_MAX_STREAMS; ++i) e[i] = stream_entry(ep.sm, min(i, ep.sm.count - 1));
+#pragma unroll
+                for (int i = 0; i < SJD_MAX_STREAMS; ++i) n_e[i] = *as_global(e[i].n);
+#pragma unroll
+                for (int i = 0; i < SJD_MAX_STREAMS; ++i)
+                    if (i == stream && i < ep.sm.count) { n_s = n_e[i]; pre.cache = as_global(e[i].kvc) + ep.layer_off; }
+            }
         }
         pre.pos = min(n_s + pre.row, ep.max_seq - 1);   // rows past the window are computed but never stored
         // (V fragments fetch factors they do not use: no branch around the loads)
@@ -129,21 +148,21 @@ __device__ __forceinline__ void apply_epilogue(const SjdGemmEpi &ep, int N, int 
                 *reinterpret_cast<float2 *>(q) = make_float2(r0, r1);
                 *reinterpret_cast<float2 *>(q + half) = make_float2(r0p, r1p);
             } else if (pre.row < ep.rows_valid && pre.cache) {
-                bf16_t *rec = pre.cache + kv_block_off(head, pos >> 5, ep.nblk, hd);
+                SJD_GLOBAL bf16_t *rec = pre.cache + kv_block_off(head, pos >> 5, ep.nblk, hd);
                 const int kk = pos & 31;
                 float la, lb, dummy0, dummy1;
                 uint32_t hi = pack_hi2(r0, r1, la, lb);
-                *reinterpret_cast<uint32_t *>(rec + kv_k_off(kk, j, hd, 0)) = hi;
-                *reinterpret_cast<uint32_t *>(rec + kv_k_off(kk, j, hd, 1)) = pack_hi2(la, lb, dummy0, dummy1);
+                *reinterpret_cast<SJD_GLOBAL uint32_t *>(rec + kv_k_off(kk, j, hd, 0)) = hi;
+                *reinterpret_cast<SJD_GLOBAL uint32_t *>(rec + kv_k_off(kk, j, hd, 1)) = pack_hi2(la, lb, dummy0, dummy1);
                 hi = pack_hi2(r0p, r1p, la, lb);
-                *reinterpret_cast<uint32_t *>(rec + kv_k_off(kk, j + half, hd, 0)) = hi;
-                *reinterpret_cast<uint32_t *>(rec + kv_k_off(kk, j + half, hd, 1)) = pack_hi2(la, lb, dummy0, dummy1);
+                *reinterpret_cast<SJD_GLOBAL uint32_t *>(rec + kv_k_off(kk, j + half, hd, 0)) = hi;
+                *reinterpret_cast<SJD_GLOBAL uint32_t *>(rec + kv_k_off(kk, j + half, hd, 1)) = pack_hi2(la, lb, dummy0, dummy1);
             }
         } else if (pre.row < ep.rows_valid && pre.cache) {
             // V: natural feature order
             const int col = n0 - 2 * d;
             const int head = col / hd, dim = col % hd;
-            bf16_t *rec = pre.cache + kv_block_off(head, pos >> 5, ep.nblk, hd);
+            SJD_GLOBAL bf16_t *rec = pre.cache + kv_block_off(head, pos >> 5, ep.nblk, hd);
             const int kk = pos & 31;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {

@@ -103,11 +103,19 @@ struct SjdStreams {
     SjdStreamEntry first;           // stream 0
     const SjdStreamEntry *table;    // device [count]: every stream (entry 0 repeats `first`); unused when count <= 1
 };
+// A pointer that a kernel has read from memory (or chosen between two) as what it is, device memory: the compiler takes
+// it for a generic one, and generic (flat) accesses count as LDS accesses too, so that waiting for one of them, or for
+// an LDS read, drains everything that is in flight.
+#define SJD_GLOBAL __attribute__((address_space(1)))
+template <typename T> __device__ __forceinline__ SJD_GLOBAL T *as_global(T *p) { return (SJD_GLOBAL T *)p; }
 // entry of stream s, s uniform across the wave
 __device__ __forceinline__ SjdStreamEntry stream_entry(const SjdStreams &sm, int s)
 {
     if (s == 0) return sm.first;
-    return sm.table[s];
+    const SJD_GLOBAL SjdStreamEntry *e = as_global(sm.table) + s;
+    SjdStreamEntry r;
+    r.n = e->n; r.done = e->done; r.kvc = e->kvc;
+    return r;
 }
 
 // Activations of bf16 models are laid out in the B-operand order of v_mfma_f32_16x16x32_bf16, so that a
