@@ -9,6 +9,7 @@
 #include "sjd_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 #define ATT_TILE 64
 #define ATT_THREADS 256
@@ -174,25 +175,39 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 &hi, bf16x8 &
 }
 
 #define AW 4
-// What the workgroups in flight can request bounds it, so the registers decide: two waves per SIMD (at most 256 each) for
-// heads of 128 and 32 queries.  Left alone the compiler took 316 (one workgroup per CU: 35.7 us at 1240 positions x 2
-// contexts of 32 queries, 27.1 now; a 7B forward of 32 drafts 3845 -> 3756): the scores of every query tile come first, so
-// that the key tiles' registers are free before the probabilities are made.
+// Up to about 1000 positions a launch is one round of latencies (arguments, cache length, K and V, merge); above, what the
+// workgroups in flight can request bounds it.  Hence:
+//  - two waves per SIMD, at most 256 registers each (left alone the compiler took 316 for heads of 128 and 32 queries, one
+//    workgroup per CU): the scores of every query tile come first, so that the key tiles' registers are free before the
+//    probabilities are made (1240 positions x 2 contexts of 32 queries: 35.7 -> 27.1 us);
+//  - loads in the order of their use (Q, K, V; the next block's K during the probabilities), as global accesses with
+//    nothing conditional between a load and its use, so that each wait is for its own loads only; and the arguments of the
+//    first loads in registers (16 queries at 600 positions: 8.3 -> 6.7 us; 7B forward of 16 drafts there 2998 -> 2942).
 // partial record of (head, split): O[MT*16][HD] unnormalised, then m[MT*16], then l[MT*16]
 template <int HD, int MT>
-__global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const float *__restrict__ qact, SjdStreams sm,
-                                                            size_t layer_off, int d, int nblk_cache, int rows,
-                                                            int splits, int qgroups, float *__restrict__ part)
+__global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n0, const int32_t *done0, const bf16_t *kvc0,
+                                                            const float *__restrict__ qact, int d, int nblk_cache,
+                                                            int rows, int splits, int qgroups, int shift,
+                                                            float *__restrict__ part, const SjdStreamEntry *table,
+                                                            size_t layer_off)
 {
+    // (n0, done0, kvc0: stream 0, its cache at this layer; they and all that every workgroup needs at once are the
+    // 16 registers of arguments that arrive with the dispatch, in front of the first dependent load)
     // blockIdx.z = (stream, query group): the stream has its own cache and cache length and its queries in
     // rows (stream << shift)..; a stream with more than MT * 16 rows is covered by several groups of
     // MT * 16 consecutive queries, each walking the keys on its own
-    const int stream = blockIdx.z / qgroups, qbase = (blockIdx.z % qgroups) * (MT * 16);
-    const SjdStreamEntry ent = stream_entry(sm, stream);
-    if (*ent.done) return;
-    const int n = *ent.n;
-    const bf16_t *__restrict__ kvc = ent.kvc + layer_off;
-    const int row0 = (stream << sm.shift) + qbase;
+    const int stream = qgroups == 1 ? (int)blockIdx.z : (int)blockIdx.z / qgroups;
+    const int qbase = ((int)blockIdx.z - stream * qgroups) * (MT * 16);
+    const SJD_GLOBAL int32_t *np = as_global(n0), *dp = as_global(done0);
+    const SJD_GLOBAL bf16_t *kvc = as_global(kvc0);
+    if (stream) {
+        const SJD_GLOBAL SjdStreamEntry *e = as_global(table) + stream;
+        np = as_global(e->n); dp = as_global(e->done); kvc = as_global((const bf16_t *)e->kvc) + layer_off;
+    }
+    const int done = *dp, n = *np;
+    asm volatile("" ::"s"(done), "s"(n));         // (one round trip for both: the length is not fetched behind the branch)
+    if (done) return;
+    const int row0 = (stream << shift) + qbase;
     part += (size_t)blockIdx.z * gridDim.x * splits * (MT * 16 * HD + 2 * MT * 16);
     constexpr int KS = HD / 32;      // k-steps of the score product
     constexpr int DT = HD / 16;      // output dim tiles
@@ -200,7 +215,7 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const float *__r
     __shared__ float m_all[AW][MT * 16], l_all[AW][MT * 16];
     __shared__ f32x4 o_slot[AW][DT][64];
     __shared__ bf16x8 q_lds[MT][KS][2][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, c = lane & 15;
     const int head = blockIdx.x, split = blockIdx.y;
     const int total = n + rows;
     const int nblk = (total + 31) >> 5;
@@ -208,40 +223,50 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const float *__r
     const int b_beg = split * bps, b_end = min(nblk, b_beg + bps);
     const float scale = rsqrtf((float)HD);
 
-    // the first block's K and V tiles are requested before anything else, so that their latency
-    // overlaps the staging of Q
+    // Loads return in order: Q first (it does not wait for the cache length either), so that it is staged while the
+    // first block's tiles are on their way, then K, then V.
+    constexpr int QU = (MT * KS + AW - 1) / AW;          // (tile, lane) units of Q a thread stages
+    float4 qx[QU][2];
+#pragma unroll
+    for (int i = 0; i < QU; ++i) {
+        const int u = min((int)threadIdx.x + i * 64 * AW, MT * KS * 64 - 1), l = u & 63, ks = (u >> 6) % KS, mt = (u >> 6) / KS;
+        // (query rows past the stream's `rows` are masked below; the clamp keeps their loads inside qact)
+        const int qr = min(row0 + mt * 16 + (l & 15), SJD_ROWS_MAX - 1);
+        const float4 *src = reinterpret_cast<const float4 *>(qact + (size_t)qr * d + head * HD + ks * 32 + (l >> 4) * 8);
+        qx[i][0] = src[0]; qx[i][1] = src[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     bf16x8 ka[2][KS][2], va[DT][2];
-    auto load_block = [&](int blk) {
-        const bf16x8 *rec = reinterpret_cast<const bf16x8 *>(kvc + kv_block_off(head, blk, nblk_cache, HD)) + lane;
+    auto load_k = [&](int blk) {
+        const SJD_GLOBAL bf16x8 *rec = reinterpret_cast<const SJD_GLOBAL bf16x8 *>(kvc + kv_block_off(head, blk, nblk_cache, HD)) + lane;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                 for (int pl = 0; pl < 2; ++pl) ka[h][ks][pl] = rec[((h * KS + ks) * 2 + pl) * 64];
+    };
+    auto load_v = [&](int blk) {
+        const SJD_GLOBAL bf16x8 *rec = reinterpret_cast<const SJD_GLOBAL bf16x8 *>(kvc + kv_block_off(head, blk, nblk_cache, HD)) + lane;
 #pragma unroll
         for (int t = 0; t < DT; ++t)
 #pragma unroll
             for (int pl = 0; pl < 2; ++pl) va[t][pl] = rec[(2 * KS * 2 + t * 2 + pl) * 64];
     };
-    int blk = b_beg + wave;
-    if (blk < b_end) load_block(blk);
-
     // Q as B operand, shared by the waves: entry [mt][ks][plane][lane] holds
     // Q[query c (+16 mt)][32 ks + 8 g .. +8], scaled by 1/sqrt(HD), as hi and lo bf16 planes
-    for (int u = threadIdx.x; u < MT * KS * 64; u += 64 * AW) {
-        const int l = u & 63, ks = (u >> 6) % KS, mt = (u >> 6) / KS;
-        float x[8];
-        // (query rows past the stream's `rows` are masked below; the clamp keeps their loads inside qact)
-        const int qr = min(row0 + mt * 16 + (l & 15), SJD_ROWS_MAX - 1);
-        const float4 *src = reinterpret_cast<const float4 *>(qact + (size_t)qr * d + head * HD + ks * 32 + (l >> 4) * 8);
-        const float4 x0 = src[0], x1 = src[1];
-        x[0] = x0.x * scale; x[1] = x0.y * scale; x[2] = x0.z * scale; x[3] = x0.w * scale;
-        x[4] = x1.x * scale; x[5] = x1.y * scale; x[6] = x1.z * scale; x[7] = x1.w * scale;
-        bf16x8 hi, lo;
-        split8(x, hi, lo);
-        q_lds[mt][ks][0][l] = hi; q_lds[mt][ks][1][l] = lo;
-    }
+    auto stage_q = [&]() {
+#pragma unroll
+        for (int i = 0; i < QU; ++i) {
+            const int u = threadIdx.x + i * 64 * AW;
+            if (u >= MT * KS * 64) break;
+            const float x[8] = {qx[i][0].x * scale, qx[i][0].y * scale, qx[i][0].z * scale, qx[i][0].w * scale,
+                                qx[i][1].x * scale, qx[i][1].y * scale, qx[i][1].z * scale, qx[i][1].w * scale};
+            bf16x8 hi, lo;
+            split8(x, hi, lo);
+            q_lds[(u >> 6) / KS][(u >> 6) % KS][0][u & 63] = hi; q_lds[(u >> 6) / KS][(u >> 6) % KS][1][u & 63] = lo;
+        }
+    };
 
     f32x4 o[MT][DT];
     float m_run[MT], l_run[MT];
@@ -251,9 +276,13 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const float *__r
 #pragma unroll
         for (int t = 0; t < DT; ++t) o[mt][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
-    __syncthreads();                              // q_lds ready
-
-    while (blk < b_end) {
+    int blk = b_beg + wave;
+    // One block.  The next block's K tiles are requested as soon as the scores have left their registers, its V tiles
+    // as soon as this block's output has left theirs; the wave's last block has a copy of the code of its own (loads
+    // behind a branch would make every wait drain them all).
+    // (Not with 32 queries on heads of 128: 256 registers do not hold it.)
+    constexpr bool AHEAD = MT * HD < 256;
+    auto block = [&](auto more) {
         const int k0 = blk * 32;
         // scores of all query tiles first: the K tiles' registers are free before the probabilities are made
         f32x4 sc[MT][2];
@@ -271,6 +300,7 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const float *__r
                 }
             }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (more.value && AHEAD) { load_k(blk + AW); __builtin_amdgcn_sched_barrier(0); }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const f32x4 (&s_)[2] = sc[mt];
@@ -307,8 +337,24 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const float *__r
                 o[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[t][0], ph, o[mt][t], 0, 0, 0);
             }
         }
-        blk += AW;
-        if (blk < b_end) load_block(blk);
+        if constexpr (more.value) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (!AHEAD) load_k(blk + AW);
+            load_v(blk + AW);
+        }
+    };
+    if (blk < b_end) {
+        load_k(blk);
+        __builtin_amdgcn_sched_barrier(0);
+        load_v(blk);
+        __builtin_amdgcn_sched_barrier(0);
+        stage_q();
+        __syncthreads();                          // q_lds ready
+        for (; blk + AW < b_end; blk += AW) block(std::true_type{});
+        block(std::false_type{});
+    } else {                                      // (a wave without a block: the same barrier)
+        stage_q();
+        __syncthreads();
     }
 
     // ---- merge the AW waves (wave order) and write the partial record -----------------------------
@@ -443,8 +489,8 @@ static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t 
     const int splits = pairs <= 2 ? kv->att_splits : std::max(1, 2 * kv->att_splits / pairs);
     if (pairs * splits > 2 * std::max(kv->att_splits, SJD_MAX_STREAMS / 2)) return SJD_EINVAL;    // (what att_part holds)
     const int grows = std::min(rows, MT * 16);
-    SJD_LAUNCH((attn_split_kernel<HD, MT>), dim3(H, splits, pairs), dim3(64 * AW), 0, s, kv->qact, sm, off, d,
-                       kv->nblk, rows, splits, qgroups, kv->att_part);
+    SJD_LAUNCH((attn_split_kernel<HD, MT>), dim3(H, splits, pairs), dim3(64 * AW), 0, s, sm.first.n, sm.first.done,
+                       sm.first.kvc + off, kv->qact, d, kv->nblk, rows, splits, qgroups, sm.shift, kv->att_part, sm.table, off);
     HIP_TRY(hipGetLastError());
     SJD_LAUNCH((attn_merge_kernel<HD, MT>), dim3(H, (grows * (HD / 4) + 255) / 256, pairs), dim3(256), 0, s, kv->att_part,
                        splits, d, rows, kv->att_out, sm.shift, qgroups, lo16 ? 1 : 0);
