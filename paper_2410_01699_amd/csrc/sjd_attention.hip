@@ -495,7 +495,10 @@ static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t 
     // (stream, query group) pairs: the partial-record buffer holds two of them at att_splits key splits;
     // more of them share it by splitting their keys less finely
     const int qgroups = (rows + MT * 16 - 1) / (MT * 16), pairs = sm.count * qgroups;
-    const int splits = pairs <= 2 ? kv->att_splits : std::max(1, 2 * kv->att_splits / pairs);
+    int splits = pairs <= 2 ? kv->att_splits : std::max(1, 2 * kv->att_splits / pairs);
+    // heads of 128: two workgroups fit a CU, and a grid of one round beats finer splits (7B guided 2 x 32 at 1240 positions,
+    // 64 pairs of head and context: 16 splits, two rounds, 4771 us a forward; 8 splits 4707)
+    if (HD == 128) splits = std::max(1, std::min(splits, 512 / (H * pairs)));
     if (pairs * splits > 2 * std::max(kv->att_splits, SJD_MAX_STREAMS / 2)) return SJD_EINVAL;    // (what att_part holds)
     const int grows = std::min(rows, MT * 16);
     SJD_LAUNCH((attn_split_kernel<HD, MT>), dim3(H, splits, pairs), dim3(64 * AW), 0, s, sm.first.n, sm.first.done,
