@@ -493,12 +493,10 @@ static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t 
     const int d = m->cfg.d_model, H = m->cfg.n_heads;
     const size_t off = (size_t)layer * kv->k_layer_stride;
     // (stream, query group) pairs: the partial-record buffer holds two of them at att_splits key splits;
-    // more of them share it by splitting their keys less finely
+    // more of them share it by splitting their keys less finely.  The count depends on the number of pairs alone, so
+    // that an image has the same sums, bit for bit, whether its forward holds one pair or two.
     const int qgroups = (rows + MT * 16 - 1) / (MT * 16), pairs = sm.count * qgroups;
-    int splits = pairs <= 2 ? kv->att_splits : std::max(1, 2 * kv->att_splits / pairs);
-    // heads of 128: two workgroups fit a CU, and a grid of one round beats finer splits (7B guided 2 x 32 at 1240 positions,
-    // 64 pairs of head and context: 16 splits, two rounds, 4771 us a forward; 8 splits 4707)
-    if (HD == 128) splits = std::max(1, std::min(splits, 512 / (H * pairs)));
+    const int splits = pairs <= 2 ? kv->att_splits : std::max(1, 2 * kv->att_splits / pairs);
     if (pairs * splits > 2 * std::max(kv->att_splits, SJD_MAX_STREAMS / 2)) return SJD_EINVAL;    // (what att_part holds)
     const int grows = std::min(rows, MT * 16);
     SJD_LAUNCH((attn_split_kernel<HD, MT>), dim3(H, splits, pairs), dim3(64 * AW), 0, s, sm.first.n, sm.first.done,
