@@ -378,19 +378,6 @@ void sjd_wide_plan(const SjdLinear *lin, int mt, size_t part_elems, int *g_out, 
     *g_out = g; *ks_out = ks; *kps_out = kps;
 }
 
-// Floats the K-slices of one layer take at most, over all row counts.  (With less room the plan above cuts K into fewer
-// slices: 7B QKV at 128 rows on three instead of four, 192 workgroups for 256 CUs.)
-size_t sjd_wide_part_elems(const SjdLinear *lin)
-{
-    size_t most = 0;
-    for (int mt = 2; mt <= SJD_MTILES; mt += 2) {
-        int g, ks, kps;
-        sjd_wide_plan(lin, mt, SIZE_MAX, &g, &ks, &kps);
-        most = std::max(most, (size_t)mt * 16 * lin->N * ks);
-    }
-    return most;
-}
-
 // The whole-K variant: three waves per workgroup, two-tile weight groups, activations in the 3-byte form, up to 32
 // rows, epilogue in the kernel.  Stages of 6 k-steps (12 activation tiles, four per wave).
 #define WIDE3_KU 6
