@@ -505,7 +505,7 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     e_qkv.d = d; e_qkv.hd = m->hd; e_qkv.nblk = kv->nblk; e_qkv.rows_valid = rows_valid; e_qkv.max_seq = m->cfg.max_seq;
     e_res.kind = SJD_EPI_RESID; e_res.out = kv->x; e_res.out24 = kv->x24; e_res.ssq_out = kv->ssq; e_res.lo16 = lo16;
     e_silu.kind = SJD_EPI_SILU; e_silu.ffn = kv->ffn; e_silu.F = F; e_silu.lo16 = down_wide;
-    e_lm.kind = SJD_EPI_STORE; e_lm.out = logits;
+    e_lm.kind = SJD_EPI_STORE; e_lm.out = logits; e_lm.rows_out = grows;
     const void *x = kv->x24, *att = kv->att_out, *ffn = kv->ffn;     // hi / lo planes, 3 bytes per value
     // x24 holds x * (gain of the normalisation the next projection sits behind), kv->ssq its partial
     // sums of squares: written by the embedding kernel for the first layer, by each residual epilogue
@@ -1420,7 +1420,7 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
         lin.w = g.Wp;
         SjdGemmEpi ep;
         memset(&ep, 0, sizeof(ep));
-        ep.kind = SJD_EPI_STORE; ep.out = g.out;
+        ep.kind = SJD_EPI_STORE; ep.out = g.out; ep.rows_out = M;
         SJD_TRY(sjd_launch_gemm_bf16(&lin, g.Ap, wide ? SJD_ACT_P4 : dtype == 2 ? SJD_ACT_P3 : SJD_ACT_F32, nullptr, 0.f, M, ep,
                                      (float *)g.part, part_elems, s));
     } else {
@@ -1534,7 +1534,7 @@ extern "C" int sjd_gemm_bench(int32_t M, int32_t N, int32_t K, int32_t tn, int32
     else { lin.wk = wk; lin.u = u; }
     SjdGemmEpi ep;
     memset(&ep, 0, sizeof(ep));
-    ep.kind = SJD_EPI_STORE; ep.out = g.out;
+    ep.kind = SJD_EPI_STORE; ep.out = g.out; ep.rows_out = rows;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIP_TRY(hipEventCreate(&e0));
     if (hipError_t e = hipEventCreate(&e1); e != hipSuccess) { (void)hipEventDestroy(e0); sjd_set_hip_error(e, "hipEventCreate"); return SJD_EHIP; }

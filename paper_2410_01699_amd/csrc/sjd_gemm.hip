@@ -6,7 +6,7 @@
 // fp32: out[m][n] = sum_k A[m][k] W[n][k]; one wave per output feature, lanes split k by float4
 template <int MR>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ W, const float *__restrict__ A, int N,
-                                                       int K, float *__restrict__ out, const SjdState *st)
+                                                       int K, int rows, float *__restrict__ out, const SjdState *st)
 {
     if (st && st->done) return;
     const int lane = threadIdx.x & 63;
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     for (int m = 0; m < MR; ++m) {
         float v = acc[m];
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) out[(size_t)m * N + n] = v;
+        if (lane == 0 && m < rows) out[(size_t)m * N + n] = v;
     }
 }
 
@@ -41,9 +41,9 @@ int sjd_launch_gemm(int32_t dtype, const SjdLinear *lin, const void *act, int32_
         if (K % 4) return SJD_EINVAL;
         dim3 grid((N + 3) / 4), block(256);
         const float *W = (const float *)lin->w, *A = (const float *)act;
-        if (rows <= 8) SJD_LAUNCH(gemm_f32_kernel<8>, grid, block, 0, s, W, A, N, K, part, st);
-        else if (rows <= 16) SJD_LAUNCH(gemm_f32_kernel<16>, grid, block, 0, s, W, A, N, K, part, st);
-        else SJD_LAUNCH(gemm_f32_kernel<32>, grid, block, 0, s, W, A, N, K, part, st);
+        if (rows <= 8) SJD_LAUNCH(gemm_f32_kernel<8>, grid, block, 0, s, W, A, N, K, rows, part, st);
+        else if (rows <= 16) SJD_LAUNCH(gemm_f32_kernel<16>, grid, block, 0, s, W, A, N, K, rows, part, st);
+        else SJD_LAUNCH(gemm_f32_kernel<32>, grid, block, 0, s, W, A, N, K, rows, part, st);
         HIP_TRY(hipGetLastError());
         return SJD_OK;
     }

@@ -113,7 +113,7 @@ template <int EPI>
 __device__ __forceinline__ void apply_epilogue(const SjdGemmEpi &ep, int N, int m, int n0, f32x4 v, const EpiPre &pre)
 {
     if (EPI == SJD_EPI_STORE) {
-        *reinterpret_cast<f32x4 *>(ep.out + (size_t)m * N + n0) = v;
+        if (m < ep.rows_out) *reinterpret_cast<f32x4 *>(ep.out + (size_t)m * N + n0) = v;
     } else if (EPI == SJD_EPI_RESID) {
         const f32x4 y = pre.x + v;
         *reinterpret_cast<f32x4 *>(ep.out + act_off(m, n0, N / 32)) = y;

@@ -239,7 +239,8 @@ struct SjdGemmEpi {
     int32_t kind;
     SjdStreams sm;               // QKV: who owns which rows
     size_t layer_off;            // QKV: element offset of this layer inside every stream's cache
-    float *out;                  // STORE / RESID: [rows][N]
+    float *out;                  // STORE: [rows_out][N]; RESID: the residual stream, whole 16-row tiles
+    int32_t rows_out;            // STORE: rows of `out`: the rows of a tile behind them are computed, not written
     void *out24;                 // RESID: planes of (updated rows) * gain_next, or NULL: none of the three
     const bf16_t *gain_next;     // RESID: [N] gain of the normalisation that follows
     float *ssq_out;              // RESID: [rows][ssq_stride(N)] sum of squares of the updated rows per 16 features
