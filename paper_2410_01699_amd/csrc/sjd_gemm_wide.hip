@@ -318,8 +318,13 @@ int sjd_gemm_wide_setup()
 
 // Column groups of both kernels' grids.  Workgroup i of a launch runs on XCD i % 8: with a multiple of eight column
 // groups the K-slices of a group and its epilogue share an L2, so the count is rounded up (the added workgroups return
-// at once) where all workgroups of the first kernel are resident together, one per CU (775M QKV at 128 rows, 36 groups:
-// 14.3 -> 13.1 us for the pair; 7B gate/up at 128 rows, 172 groups x 2 slices: 62.7 -> 69.4 us, so not there).
+// at once) where all workgroups of the first kernel are resident together, one per CU, and there are 32 groups or more.
+// Both kernels together, alone on cold weights, not rounded and rounded:
+//   775M QKV, 36 groups x 6 slices: 10.8 -> 9.8 us at 64 rows, 12.5 -> 11.0 at 96, 14.8 -> 13.1 at 128
+//   7B gate/up up to 64 rows, 86 x 2: 42.9 -> 41.0 in one run, 46.1 -> 45.7 in another; at 128 rows, 172 x 2 and so not
+//   resident together: 65.4 and 65.0, a forward of 8 x 16 rows 6722 and 6696 (no more than runs differ)
+//   775M O and down, 12 groups: alone 8.5 -> 8.0 and 11.1 -> 10.5, but a forward of 4 x 16 rows 1512 -> 1532 and a prompt
+//   of 121 1871 -> 1907 (rounded to 16, four XCDs have two groups and four have one)
 static int wide_cols(int groups, int g, int ks)
 {
     const int cols = (groups + WIDE_WAVES * g - 1) / (WIDE_WAVES * g), up = (cols + 7) & ~7;
