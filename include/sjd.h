@@ -235,8 +235,8 @@ int sjd_forward_logits(sjd_model *m, sjd_kv *kv, const int32_t *tokens, int32_t 
 
 /* The same for B handles in one forward: tokens dev [B x L], logits dev [B x L x V_s] (of guided handles:
  * the guided logits).  A handle
- * inside a generation (sjd_decode_begin) whose image is complete is skipped: its rows of `logits`
- * are left as they are.                                                                          */
+ * inside a generation (sjd_decode_begin) whose image is complete takes no part: what its rows of
+ * `logits` hold afterwards means nothing.                                                        */
 int sjd_forward_logits_batch(sjd_model *m, sjd_kv *const *kvs, int32_t B, const int32_t *tokens, int32_t L,
                              float *logits, void *stream);
 

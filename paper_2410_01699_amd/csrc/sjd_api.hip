@@ -415,7 +415,7 @@ static int g_lo16_from_rows = SJD_LO16_FROM_ROWS;
 static bool rows_use_lo16(int grows) { return grows >= g_lo16_from_rows; }
 
 // ---- the window forward (Step 2) ------------------------------------------------------------
-// rows = rows computed (<= 32), rows_valid = rows whose K/V are written.  Inputs already in kv->x.
+// rows = rows computed, rows_valid = rows whose K/V are written.  Inputs already in kv->x.
 static double lin_bytes(const sjd_model *m, const SjdLinear &l) { return (double)l.N * l.K * elt_size(m->cfg.dtype); }
 
 // `stream` selects the cache and the cache length the rows are positioned with (0 conditional,
@@ -857,7 +857,7 @@ extern "C" int sjd_decode_steps(sjd_model *m, sjd_kv *kv, int32_t n_steps, void 
 
 // ---- batched decoding: B handles share every window forward --------------------------------------
 // rows reserved per handle: the smallest power of two that holds the window, such that all fit in
-// the 32 rows one projection launch computes
+// the SJD_ROWS_MAX rows one forward computes
 static int batch_shift(int32_t B, int32_t L)
 {
     for (int shift = 0; shift <= 6; ++shift)

@@ -189,7 +189,7 @@ __device__ __forceinline__ void arrive_and_wait()
 // workgroups in flight can request bounds it.  Hence:
 //  - two waves per SIMD, at most 256 registers each (left alone the compiler took 316 for heads of 128 and 32 queries, one
 //    workgroup per CU): the scores of every query tile come first, so that the key tiles' registers are free before the
-//    probabilities are made (1240 positions x 2 contexts of 32 queries: 35.7 -> 27.1 us);
+//    probabilities are made (1240 positions x 2 contexts of 32 queries: 35.7 -> 27.1 us, 23.1 with what follows);
 //  - loads in the order of their use (Q, K, V; the next block's K during the probabilities), as global accesses with
 //    nothing conditional between a load and its use, so that each wait is for its own loads only; and the arguments of the
 //    first loads in registers (16 queries at 600 positions: 8.3 -> 6.7 us; 7B forward of 16 drafts there 2998 -> 2942).
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
                                                             size_t layer_off)
 {
     // (n0, done0, kvc0: stream 0, its cache at this layer; they and all that every workgroup needs at once are the
-    // 16 registers of arguments that arrive with the dispatch, in front of the first dependent load)
+    // 14 registers of arguments that arrive with the dispatch, in front of the first dependent load)
     // blockIdx.z = (stream, query group): the stream has its own cache and cache length and its queries in
     // rows (stream << shift)..; a stream with more than MT * 16 rows is covered by several groups of
     // MT * 16 consecutive queries, each walking the keys on its own
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
 // the hi / lo operand planes the O projection streams (act24_idx).  All loads of a thread are issued before anything
 // depends on them (splits <= ATT_MAX_SPLITS), four splits at a time; one wave per workgroup, so that the records are read
 // by as many CUs as there are waves (four waves each, and the loads of all 16 splits whatever their number: 7B forward
-// of 16 drafts 2945 us, now 2893; 775M 838, now 821).
+// of 16 drafts 2945 us, now 2893; 775M 838, now 821; in a kernel trace the kernel itself is 5.1 and 4.9).
 #define ATT_MAX_SPLITS 16
 #define ATT_MERGE_THREADS 64
 template <int HD, int MT>
