@@ -100,6 +100,9 @@ typedef struct {
 int sjd_init_model(const sjd_config *cfg, const void *host_weights, size_t nbytes, sjd_model **out);
 void sjd_free_model(sjd_model *m);
 
+/* A handle holds its cache and scratch for forwards of up to SJD_MAX_ROWS rows: at 7B about 75 MB besides the
+ * cache and the rows of logits (45 of them partial sums of the projections), used by its own prompts and
+ * iterations and, in a batch, by those of the batch's first handle for all.                     */
 int sjd_kv_create(const sjd_model *m, sjd_kv **out);
 void sjd_kv_free(sjd_kv *kv);
 int sjd_kv_reset(sjd_kv *kv);                     /* n = 0                                       */

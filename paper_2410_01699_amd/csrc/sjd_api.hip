@@ -239,8 +239,13 @@ extern "C" int sjd_kv_create(const sjd_model *m, sjd_kv **out)
     A(kv->ssq, c.dtype == 1 ? R * ssq_stride((int)d) * 4 : 16);
     A(kv->h, c.dtype == 0 ? R * d * 4 : 16);
     // fp32 models: the output of a linear layer; bf16 models: the fp32 sums of the wide projection kernel's
-    // K-slices (two full outputs' worth: shapes with few output features split K further)
-    if (c.dtype == 1) kv->part_elems = 2 * part;
+    // K-slices, as many of them as any linear layer is cut into at any row count
+    if (c.dtype == 1) {
+        kv->part_elems = 0;
+        auto upd_wide = [&](const SjdLinear &l) { kv->part_elems = std::max(kv->part_elems, sjd_wide_part_elems(&l)); };
+        for (int l = 0; l < c.n_layers; ++l) { upd_wide(m->layers[l].qkv); upd_wide(m->layers[l].o); upd_wide(m->layers[l].gu); upd_wide(m->layers[l].down); }
+        upd_wide(m->lm);
+    }
     A(kv->part, kv->part_elems * 4);
     A(kv->qact, R * d * 4);
     A(kv->att_part, sjd_attention_part_elems(m) * 4);

@@ -322,8 +322,8 @@ int sjd_gemm_wide_setup()
 // at once) where all workgroups of the first kernel are resident together, one per CU, and there are 32 groups or more.
 // Both kernels together, alone on cold weights, not rounded and rounded:
 //   775M QKV, 36 groups x 6 slices: 10.8 -> 9.8 us at 64 rows, 12.5 -> 11.0 at 96, 14.8 -> 13.1 at 128
-//   7B gate/up up to 64 rows, 86 x 2: 42.9 -> 41.0 in one run, 46.1 -> 45.7 in another; at 128 rows, 172 x 2 and so not
-//   resident together: 65.4 and 65.0, a forward of 8 x 16 rows 6722 and 6696 (no more than runs differ)
+//   7B gate/up up to 64 rows, 86 x 2: 42.9 -> 41.0 in one run, 46.1 -> 45.7 in another; at 128 rows, 172 x 4 and so not
+//   resident together: 61.6 -> 68.5, a forward of 8 x 16 rows 6650 -> 6891
 //   775M O and down, 12 groups: alone 8.5 -> 8.0 and 11.1 -> 10.5, but a forward of 4 x 16 rows 1512 -> 1532 and a prompt
 //   of 121 1871 -> 1907 (rounded to 16, four XCDs have two groups and four have one)
 static int wide_cols(int groups, int g, int ks)
@@ -382,6 +382,22 @@ void sjd_wide_plan(const SjdLinear *lin, int mt, size_t part_elems, int *g_out, 
     kps = (kps + ku - 1) / ku * ku;             // whole stages
     ks = (KT + kps - 1) / kps;
     *g_out = g; *ks_out = ks; *kps_out = kps;
+}
+
+// Floats the K-slices of one layer take at most, over all row counts.  With less room the plan above cuts K into fewer
+// slices: with two outputs of the widest layer 7B QKV at 128 rows on three instead of four, 192 workgroups for 256 CUs, and
+// gate/up on two.  A forward of 8 x 16 rows 6628 us so, 6351 as it is; prompt of 125 5843 and 5560.  The error against 64
+// bits falls with the slices, which are shorter chains of fp32 sums: QKV 3.24e-7 (2-norm) on three, gate/up 3.97e-7 on two,
+// both 2.80e-7 on four.
+size_t sjd_wide_part_elems(const SjdLinear *lin)
+{
+    size_t most = 0;
+    for (int mt = 2; mt <= SJD_MTILES; mt += 2) {
+        int g, ks, kps;
+        sjd_wide_plan(lin, mt, SIZE_MAX, &g, &ks, &kps);
+        most = std::max(most, (size_t)mt * 16 * lin->N * ks);
+    }
+    return most;
 }
 
 // The whole-K variant: three waves per workgroup, two-tile weight groups, activations in the 3-byte form, up to 32

@@ -375,6 +375,7 @@ int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq
 int sjd_launch_gemm_wide3(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
                           const SjdGemmEpi &ep, hipStream_t s);
 void sjd_wide_plan(const SjdLinear *lin, int mt, size_t part_elems, int *g_out, int *ks_out, int *kps_out);
+size_t sjd_wide_part_elems(const SjdLinear *lin);
 int sjd_gemm_wide_setup();
 int sjd_bf16_rows_to_f32(const bf16_t *src, int32_t rows, int32_t K, float *dst, hipStream_t s);
 int sjd_f32_rows_to_act24(const float *src, int32_t rows, int32_t K, void *dst, bool lo16, hipStream_t s);

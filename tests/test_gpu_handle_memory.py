@@ -13,8 +13,8 @@ MIB = 1 << 20
 
 def test_handle_of_7b_widths():
     """One layer of the 7B widths, 256 positions.  By the sizes in sjd_kv_create: cache 8 MiB, K-slices of the widest
-    projection 21.5 (two outputs of 128 x 22016), FFN hidden 5.4, attention records 4.1, six [128 x 4096] matrices 12,
-    rows of 256 logits 0.8: 52 MiB.  12 MiB more for the allocator's granularity (28 allocations)."""
+    projection 43 (four outputs of 128 x 22016), FFN hidden 5.4, attention records 4.1, six [128 x 4096] matrices 12, rows
+    of 256 logits 0.8: 74 MiB.  12 MiB more for the allocator's granularity (28 allocations)."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2410_01699_amd import binding as B
@@ -26,7 +26,7 @@ def test_handle_of_7b_widths():
         kvs += [B.sjd_kv_create(m) for _ in range(4)]
         each = (before - torch.cuda.mem_get_info()[0]) / 4
         print(f"{each / MIB:.1f} MiB a handle", flush=True, file=sys.stderr)
-        assert each < 64 * MIB
+        assert each < 86 * MIB
     finally:
         for kv in kvs:
             B.sjd_kv_free(kv)
