@@ -499,17 +499,33 @@ static int launch_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows,
     return SJD_OK;
 }
 
+// Key splits of a launch over `pairs` (stream, query group) pairs of `heads` heads.  The partial-record buffer holds two
+// pairs at att_splits splits; more of them share it by splitting their keys less finely.  Heads of 128 take the count, up to
+// that, with the least work in a row: 512 workgroups run at once (two fit a CU by their registers), so the launch is
+// ceil(workgroups / 512) rounds of 1 / splits of the keys each, and of equal counts the smallest (fewer records to merge).
+// Without and with it, 7B forwards over 3967 positions: two contexts of 16 drafts 16 splits (two rounds) 4820 us, 8 splits
+// 4757; of 32 drafts 5780 and 5713; five of 16 6 and 3 splits 8858 and 8698; eight 4 and 2 splits 11750 and 11646; six keep
+// their 5 (two rounds; 2 splits, one round, 9571 us, 5 splits 9518).  At 1239 positions two of 32: 4761 and 4702.
+static int key_splits(int hd, int heads, int pairs, int att_splits)
+{
+    const int most = pairs <= 2 ? att_splits : std::max(1, 2 * att_splits / pairs);
+    if (hd != 128) return most;
+    int best = 1, best_rounds = (heads * pairs + 511) / 512;
+    for (int s = 2; s <= most; ++s) {
+        const int rounds = (heads * pairs * s + 511) / 512;
+        if (rounds * best < best_rounds * s) { best = s; best_rounds = rounds; }
+    }
+    return best;
+}
+
 template <int HD, int MT>
 static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, const SjdStreams &sm, bool lo16,
                          hipStream_t s)
 {
     const int d = m->cfg.d_model, H = m->cfg.n_heads;
     const size_t off = (size_t)layer * kv->k_layer_stride;
-    // (stream, query group) pairs: the partial-record buffer holds two of them at att_splits key splits;
-    // more of them share it by splitting their keys less finely.  The count depends on the number of pairs alone, so
-    // that an image has the same sums, bit for bit, whether its forward holds one pair or two.
     const int qgroups = (rows + MT * 16 - 1) / (MT * 16), pairs = sm.count * qgroups;
-    const int splits = pairs <= 2 ? kv->att_splits : std::max(1, 2 * kv->att_splits / pairs);
+    const int splits = key_splits(HD, H, pairs, kv->att_splits);
     if (pairs * splits > 2 * std::max(kv->att_splits, SJD_MAX_STREAMS / 2)) return SJD_EINVAL;    // (what att_part holds)
     const int grows = std::min(rows, MT * 16);
     SJD_LAUNCH((attn_split_kernel<HD, MT>), dim3(H, splits, pairs), dim3(64 * AW), 0, s, sm.first.n, sm.first.done,
