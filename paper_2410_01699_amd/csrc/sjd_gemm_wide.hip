@@ -22,9 +22,9 @@
 //    its arrival counter write back and invalidate the L2 of the XCD.)
 // At M = 128 the two MFMAs per weight tile and M-tile price the matrix cores at about 9.8 TB/s of
 // weights; measured, the kernel runs at about 30 % of the bf16 MFMA peak there: the one regime of this path where
-// matrix-core utilisation is a meaningful number.  It is at no limit that counters show: at 64 and 128 rows the CUs
-// fill their L1s from L2 with 6.2 and 8.7 TB/s (the skinny kernel reaches 9.9), LDS waits are 1 and 6 % of wave time, and
-// neither half the activation traffic (eight waves per workgroup) nor earlier requests made it faster.
+// matrix-core utilisation is a meaningful number.  What bounds it is known in part only: at 128 rows the CUs fill their
+// L1s from L2 with 10.1 TB/s, as the skinny kernel does at 32, but half the activation traffic (eight waves per
+// workgroup) gained 3 % on gate/up and lost elsewhere; at 64 rows they fill with 6.2, and LDS waits are 1 and 6 % of wave time.
 #include "sjd_gemm_epi.h"
 
 #include <algorithm>
