@@ -100,8 +100,8 @@ typedef struct {
 int sjd_init_model(const sjd_config *cfg, const void *host_weights, size_t nbytes, sjd_model **out);
 void sjd_free_model(sjd_model *m);
 
-/* A handle holds its cache and scratch for forwards of up to SJD_MAX_ROWS rows: at 7B about 75 MB besides the
- * cache and the rows of logits (45 of them partial sums of the projections), used by its own prompts and
+/* A handle holds its cache and scratch for forwards of up to SJD_MAX_ROWS rows: at 7B about 47 MB besides the
+ * cache and the rows of logits (17 of them partial sums of the projections), used by its own prompts and
  * iterations and, in a batch, by those of the batch's first handle for all.                     */
 int sjd_kv_create(const sjd_model *m, sjd_kv **out);
 void sjd_kv_free(sjd_kv *kv);
@@ -293,7 +293,9 @@ int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_t M, int32_
  * 3-byte form the model's projections read).  `tn` = output tiles
  * per workgroup (1..3), wk = waves splitting K (8 or 4; 0 = the choice the model makes), u = k-steps per
  * prefetch stage (2; 4 for wk = 4, M <= 16; 0 = the choice the model makes).
- * More than 32 rows run the wide kernel (waves split N and share the activations through LDS, K split
+ * wk = u = 0 runs the kernel that the model would: for large N (two or more workgroups per CU otherwise), and above
+ * 32 rows for most shapes, the span kernel (one workgroup per CU owns its features for the whole reduction).
+ * More than 32 rows otherwise run the wide kernel (waves split N and share the activations through LDS, K split
  * across workgroups, a second kernel adds the slices): then wk = K-slices and u = weight groups per wave
  * (0 = automatic); wk >= 100 asks for the wide kernel at any row count, with wk - 100 K-slices.  M above
  * SJD_MAX_ROWS is an off-path measurement of the wide kernel's matrix-core rate: the rows are cut into

@@ -412,13 +412,6 @@ static int window_max(const sjd_model *m, bool guided)
     return m->cfg.dtype == 1 ? w : std::min(w, SJD_ROWS_F32);
 }
 
-// Which form the activations of a forward over `grows` rows take between its kernels: the 2-byte lo plane
-// (second MFMA operand ready made, 4 bytes per value) from SJD_LO16_FROM_ROWS rows on, the 1-byte lo plane
-// (3 bytes per value, second operand rebuilt by every wave) below.  One choice per forward: every producer
-// and every consumer of a forward agree.
-static int g_lo16_from_rows = SJD_LO16_FROM_ROWS;
-static bool rows_use_lo16(int grows) { return grows >= g_lo16_from_rows; }
-
 // ---- the window forward (Step 2) ------------------------------------------------------------
 // rows = rows computed, rows_valid = rows whose K/V are written.  Inputs already in kv->x.
 static double lin_bytes(const sjd_model *m, const SjdLinear &l) { return (double)l.N * l.K * elt_size(m->cfg.dtype); }
@@ -492,14 +485,9 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     const int d = m->cfg.d_model, F = m->cfg.d_ffn;
     const float eps = m->cfg.rms_eps;
     const int grows = ((sm.count - 1) << sm.shift) + rows;      // rows the projections compute
-    // Which kernel each projection runs on decides the form of the buffer it reads (its producer writes
-    // that form): the residual stream's planes feed QKV, gate/up and the LM head, which go wide together
-    // (above SJD_ROWS_SKINNY rows); the attention output feeds O and the FFN hidden feeds down, which may go
-    // wide from fewer rows on (SjdLinear::wide_from).
-    const bool lo16 = rows_use_lo16(grows);
-    const int form = lo16 ? SJD_ACT_P4 : SJD_ACT_P3;
-    auto goes_wide = [&](const SjdLinear &lin) { return lo16 || (lin.wide_from > 0 && grows >= lin.wide_from); };
-    const bool o_wide = goes_wide(m->layers[0].o), down_wide = goes_wide(m->layers[0].down);
+    // Each projection says in which form it wants its activations (sjd_gemm_form); whoever writes them writes that form.
+    auto form = [&](const SjdLinear &lin) { return sjd_gemm_form(&lin, grows); };
+    auto lo16 = [&](const SjdLinear &lin) { return form(lin) == SJD_ACT_P4; };
     // upper bound of the K/V bytes one layer's attention reads (hi + lo planes)
     const double kv_bytes_layer = 2.0 * kv_tokens_upper * d * 4;
     SjdGemmEpi e_qkv, e_res, e_silu, e_lm;
@@ -508,8 +496,8 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     e_res = e_qkv; e_silu = e_qkv; e_lm = e_qkv;
     e_qkv.kind = SJD_EPI_QKV; e_qkv.qact = kv->qact; e_qkv.cosT = m->rope_cos; e_qkv.sinT = m->rope_sin;
     e_qkv.d = d; e_qkv.hd = m->hd; e_qkv.nblk = kv->nblk; e_qkv.rows_valid = rows_valid; e_qkv.max_seq = m->cfg.max_seq;
-    e_res.kind = SJD_EPI_RESID; e_res.out = kv->x; e_res.out24 = kv->x24; e_res.ssq_out = kv->ssq; e_res.lo16 = lo16;
-    e_silu.kind = SJD_EPI_SILU; e_silu.ffn = kv->ffn; e_silu.F = F; e_silu.lo16 = down_wide;
+    e_res.kind = SJD_EPI_RESID; e_res.out = kv->x; e_res.out24 = kv->x24; e_res.ssq_out = kv->ssq;
+    e_silu.kind = SJD_EPI_SILU; e_silu.ffn = kv->ffn; e_silu.F = F;
     e_lm.kind = SJD_EPI_STORE; e_lm.out = logits; e_lm.rows_out = grows;
     const void *x = kv->x24, *att = kv->att_out, *ffn = kv->ffn;     // hi / lo planes, 3 bytes per value
     // x24 holds x * (gain of the normalisation the next projection sits behind), kv->ssq its partial
@@ -518,16 +506,18 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     const float *ssq = kv->ssq;
     for (int l = 0; l < m->cfg.n_layers; ++l) {
         const SjdLayer &L = m->layers[l];
+        const SjdLinear &next = l + 1 < m->cfg.n_layers ? m->layers[l + 1].qkv : m->lm;
         e_qkv.layer_off = (size_t)l * kv->k_layer_stride;
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.qkv), sjd_launch_gemm_bf16(&L.qkv, x, form, ssq, eps, grows, e_qkv, kv->part, kv->part_elems, s));
-        PROF(kv, SJD_PROF_ATTENTION, kv_bytes_layer, sjd_launch_attention(m, kv, l, rows, sm, o_wide, s));
-        e_res.gain_next = (const bf16_t *)L.g2;
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm_bf16(&L.o, att, o_wide ? SJD_ACT_P4 : SJD_ACT_P3, nullptr, 0.f, grows, e_res, kv->part, kv->part_elems, s));
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.gu), sjd_launch_gemm_bf16(&L.gu, x, form, ssq, eps, grows, e_silu, kv->part, kv->part_elems, s));
-        e_res.gain_next = (const bf16_t *)(l + 1 < m->cfg.n_layers ? m->layers[l + 1].g1 : m->gf);
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.down), sjd_launch_gemm_bf16(&L.down, ffn, down_wide ? SJD_ACT_P4 : SJD_ACT_P3, nullptr, 0.f, grows, e_res, kv->part, kv->part_elems, s));
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.qkv), sjd_launch_gemm_bf16(&L.qkv, x, form(L.qkv), ssq, eps, grows, e_qkv, kv->part, kv->part_elems, s));
+        PROF(kv, SJD_PROF_ATTENTION, kv_bytes_layer, sjd_launch_attention(m, kv, l, rows, sm, lo16(L.o), s));
+        e_res.gain_next = (const bf16_t *)L.g2; e_res.lo16 = lo16(L.gu);
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm_bf16(&L.o, att, form(L.o), nullptr, 0.f, grows, e_res, kv->part, kv->part_elems, s));
+        e_silu.lo16 = lo16(L.down);
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.gu), sjd_launch_gemm_bf16(&L.gu, x, form(L.gu), ssq, eps, grows, e_silu, kv->part, kv->part_elems, s));
+        e_res.gain_next = (const bf16_t *)(l + 1 < m->cfg.n_layers ? m->layers[l + 1].g1 : m->gf); e_res.lo16 = lo16(next);
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.down), sjd_launch_gemm_bf16(&L.down, ffn, form(L.down), nullptr, 0.f, grows, e_res, kv->part, kv->part_elems, s));
     }
-    PROF(kv, SJD_PROF_GEMM, lin_bytes(m, m->lm), sjd_launch_gemm_bf16(&m->lm, x, form, ssq, eps, grows, e_lm, kv->part, kv->part_elems, s));
+    PROF(kv, SJD_PROF_GEMM, lin_bytes(m, m->lm), sjd_launch_gemm_bf16(&m->lm, x, form(m->lm), ssq, eps, grows, e_lm, kv->part, kv->part_elems, s));
     return SJD_OK;
 }
 
@@ -543,7 +533,7 @@ static int forward_window(sjd_model *m, sjd_kv *kv, const int32_t *ids, int32_t 
         const SjdStreams sm = handle_streams(kv, stream_mode, rows);
         const int32_t *idv[SJD_MAX_STREAMS] = {ids, ids};
         int32_t *errv[SJD_MAX_STREAMS] = {&kv->state->err, &kv->state->err};
-        const bool lo16 = rows_use_lo16(((sm.count - 1) << sm.shift) + rows);
+        const bool lo16 = sjd_gemm_form(&m->layers[0].qkv, ((sm.count - 1) << sm.shift) + rows) == SJD_ACT_P4;
         PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, idv, id_rows, emb_rows, rows, sm, kv->x, kv->x24, kv->ssq, errv, lo16, s));
         // (only the profiler uses the count: it has read the true lengths before the iteration)
         const double toks = kv->prof ? kv->prof_kv_tokens
@@ -940,7 +930,7 @@ static int forward_batch(sjd_model *m, sjd_kv *const *kvs, int32_t B, const int3
         for (int c = 0; c < per; ++c) { ids_s[per * b + c] = ids[b]; errv[per * b + c] = &kvs[b]->state->err; }
         kvs[b]->last_stream = s;
     }
-    const bool lo16 = rows_use_lo16(((sm.count - 1) << sm.shift) + L);
+    const bool lo16 = sjd_gemm_form(&m->layers[0].qkv, ((sm.count - 1) << sm.shift) + L) == SJD_ACT_P4;
     PROF(kv0, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, ids_s, L, nullptr, L, sm, kv0->x, kv0->x24, kv0->ssq, errv, lo16, s));
     double toks = 0;
     for (int b = 0; b < B; ++b) toks += kvs[b]->n_upper + L + (kv0->cfg_on ? kvs[b]->n_upper_u + L : 0);
@@ -1405,28 +1395,31 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
     if (dtype == 0 && K % 4) return SJD_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     const size_t es = elt_size(dtype);
-    const bool wide = dtype >= 1 && M > SJD_ROWS_SKINNY;
+    SjdLinear lin;
+    memset(&lin, 0, sizeof(lin));
+    lin.N = N; lin.K = K; lin.tn = 1; lin.w = W;
+    if (dtype >= 1) sjd_choose_tiles(&lin);
+    // bf16: operand planes in the form the kernel of this shape and row count reads (bf16 values are exact in either);
+    // bf16 activations on the skinny kernel as fp32, split on the fly
+    int form = dtype >= 1 ? sjd_gemm_form(&lin, M) : SJD_ACT_F32;
+    if (dtype == 1 && M <= SJD_ROWS_SKINNY) form = SJD_ACT_F32;
+    const bool wide = form == SJD_ACT_P4;
     GemmScratch g;
     SJD_TRY(dev_alloc(&g.Ap, (size_t)SJD_ROWS_MAX * K * 4 + 2048));   // rows past M and the tile behind stay zero
     SJD_TRY(dev_alloc((void **)&g.out, (size_t)SJD_ROWS_MAX * N * 4));
     const size_t part_elems = wide ? (size_t)8 * SJD_ROWS_MAX * N : 0;      // (room for up to 8 K-slices)
     if (wide) SJD_TRY(dev_alloc(&g.part, part_elems * 4));
-    SjdLinear lin;
-    memset(&lin, 0, sizeof(lin));
-    lin.N = N; lin.K = K; lin.tn = 1; lin.w = W;
     if (dtype >= 1) {
-        // the wide kernel reads the 3-byte planes only (exact for bf16 values: their low byte is zero)
-        if (dtype == 1 && !wide) SJD_TRY(sjd_bf16_rows_to_f32((const bf16_t *)A, M, K, (float *)g.Ap, s));
+        if (form == SJD_ACT_F32) SJD_TRY(sjd_bf16_rows_to_f32((const bf16_t *)A, M, K, (float *)g.Ap, s));
         else if (dtype == 1) SJD_TRY(sjd_bf16_rows_to_act24((const bf16_t *)A, M, K, g.Ap, s));
-        else SJD_TRY(sjd_f32_rows_to_act24((const float *)A, M, K, g.Ap, wide, s));     // hi / lo planes
+        else SJD_TRY(sjd_f32_rows_to_act24((const float *)A, M, K, g.Ap, wide, s));
         SJD_TRY(dev_alloc(&g.Wp, (size_t)N * K * es));
-        sjd_choose_tiles(&lin);
         SJD_TRY(sjd_repack_bf16((const bf16_t *)W, (bf16_t *)g.Wp, N, K, lin.tn, 0, 0, 0, s));
         lin.w = g.Wp;
         SjdGemmEpi ep;
         memset(&ep, 0, sizeof(ep));
         ep.kind = SJD_EPI_STORE; ep.out = g.out; ep.rows_out = M;
-        SJD_TRY(sjd_launch_gemm_bf16(&lin, g.Ap, wide ? SJD_ACT_P4 : dtype == 2 ? SJD_ACT_P3 : SJD_ACT_F32, nullptr, 0.f, M, ep,
+        SJD_TRY(sjd_launch_gemm_bf16(&lin, g.Ap, form, nullptr, 0.f, M, ep,
                                      (float *)g.part, part_elems, s));
     } else {
         HIP_TRY(hipMemcpyAsync(g.Ap, A, (size_t)M * K * es, hipMemcpyDeviceToDevice, s));
@@ -1534,7 +1527,7 @@ extern "C" int sjd_gemm_bench(int32_t M, int32_t N, int32_t K, int32_t tn, int32
     SjdLinear lin;
     memset(&lin, 0, sizeof(lin));
     lin.N = N; lin.K = K; lin.tn = tn; lin.w = g.Wp;
-    if (force_wide && u == 7 && rows > 16 && rows <= 32 && tn == 2) { lin.whole_k_rows = 32; form = SJD_ACT_P3; }   // the wide kernel's whole-K variant
+    if (!force_wide && chunks == 1 && wk == 0 && u == 0 && sjd_span_takes(&lin, rows)) form = SJD_ACT_P3;       // the model's choice: the span kernel
     else if (wide) { lin.wks = wk; lin.wg = u; lin.wide_from = 1; }      // wide kernel: K-slices and weight groups per wave (0 = automatic)
     else { lin.wk = wk; lin.u = u; }
     SjdGemmEpi ep;

@@ -338,8 +338,6 @@ void sjd_choose_tiles(SjdLinear *lin)
         }
     }
     lin->tn = best_tn; lin->wk = 0; lin->u = 0; lin->wg = 0; lin->wks = 0; lin->wide_from = 0;
-    // two-tile groups, at least 512 of them (N >= 16384): three per workgroup still give one workgroup to most CUs
-    lin->whole_k_rows = (best_tn == 2 && tiles / 2 >= 512) ? 32 : 0;
 }
 
 template <int MT, int TN, int WK, int U, int PRO>
@@ -374,22 +372,25 @@ static int launch_epi(const SjdLinear *lin, const void *act, const float *ssq_in
     }
 }
 
+int sjd_gemm_form(const SjdLinear *lin, int32_t rows)
+{
+    if (sjd_span_takes(lin, rows)) return SJD_ACT_P3;
+    return rows > SJD_ROWS_SKINNY || (lin->wide_from > 0 && rows >= lin->wide_from) ? SJD_ACT_P4 : SJD_ACT_P3;
+}
+
 int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const float *ssq_in, float eps, int32_t rows,
                          const SjdGemmEpi &ep, float *part, size_t part_elems, hipStream_t s)
 {
     const bool act24 = form != SJD_ACT_F32, lo16 = form == SJD_ACT_P4;
     if (rows < 1 || rows > SJD_ROWS_MAX || (ssq_in && !act24) || form < 0 || form > 2) return SJD_EINVAL;
+    if (form == SJD_ACT_P3 && !lin->wk && !lin->u && sjd_span_takes(lin, rows))
+        return sjd_launch_gemm_span(lin, act, ssq_in, eps, rows, ep, s);
     // the wide kernel: above SJD_ROWS_SKINNY rows, or from lin->wide_from rows on; it reads the 4-byte planes
     const bool wide = rows > SJD_ROWS_SKINNY || (lin->wide_from > 0 && rows >= lin->wide_from && lo16 && part);
     if (wide) {
         if (!lo16) return SJD_EINVAL;
         return sjd_launch_gemm_wide(lin, act, ssq_in, eps, rows, ep, part, part_elems, s);
     }
-    // the wide kernel's whole-K variant (shapes whose N alone fills the chip; activations in the 3-byte form)
-    // (measured inside 7B iterations: 5 % of an iteration at 32 rows; at 16 rows the skinny kernel is 2 % ahead)
-    if (rows > 16 && rows <= lin->whole_k_rows && form == SJD_ACT_P3 &&
-        (ep.kind == SJD_EPI_SILU || ep.kind == SJD_EPI_STORE) && (ssq_in || ep.kind == SJD_EPI_STORE))
-        return sjd_launch_gemm_wide3(lin, act, ssq_in, eps, rows, ep, s);
     if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
     if (lin->tn < 1 || lin->N % (16 * lin->tn) || lin->K % 32) return SJD_EINVAL;
     const int mt = rows <= 16 ? 1 : 2;

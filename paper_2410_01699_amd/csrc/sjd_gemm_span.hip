@@ -1,0 +1,263 @@
+// bf16 projections whose workgroups own a span of output features for the whole reduction, at any row count (paper
+// Sec. 4.1 Step 2): C[M x N] = A[M x K] * W^T, M = 1 .. 128.
+//
+// Like the skinny kernel, the waves of a workgroup split K, each streams its own weights and its own activation tiles
+// straight into registers (nothing is shared, so nothing is staged and no barrier stands in the loop) and the fp32 sums
+// meet once, through LDS, in wave order; the epilogue sees final values, so there are no K-slices in memory and no second
+// kernel.  Two things differ:
+//  - a workgroup owns G packed weight groups (up to six 16-feature tiles), so many that one workgroup per CU covers N.
+//    Every workgroup reads all M x K activations from L2; with the skinny kernel's two tiles the 7B gate/up projection had
+//    688 workgroups, 2.7 reads of the activations per CU.
+//  - up to eight row tiles.  A wave's activation tiles are refilled in place as soon as their products are issued, the
+//    weights of the next k-step are requested one k-step ahead.
+//
+// What bounds it, 7B gate/up (180 MB) alone on cold weights: up to 32 rows the weight stream (16 rows 29.8 us, 32 rows 31.5;
+// a kernel that only reads these bytes from as many workgroups 28; the skinny kernel was at 31.2 and 40.3).  Above, the
+// activations, which every workgroup reads from L2 in between (64 rows 38.6 us, 128 rows 57; without them 33 and 36, without
+// the products 36.5 and 48): loads return in order, so tiles that hit L2 wait for weights that do not.  The wide kernel and its
+// second kernel need 46 and 62-65 us.  Inside a forward, per launch: 29.2 us at 16 rows (skinny 32.2), 31.0 at 32 (the wide
+// kernel with final sums in it 38.5), 37.6 at 64 (wide 40.7 + 5.3), 58.7 at 128 (wide 55.8 + 9.5).
+#include "sjd_gemm_epi.h"
+
+#include <algorithm>
+
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
+
+constexpr int pow2_floor(int x) { int p = 1; while (p * 2 <= x) p *= 2; return p; }
+
+// second operand of 8 values from their hi plane entry and their byte plane entry (as lo_from_byte_plane)
+__device__ __forceinline__ bf16x8 lo_by_perm(bf16x8 hi, u32x2_t lo8)
+{
+    const u32x4_t hw = __builtin_bit_cast(u32x4_t, hi);
+    u32x4_t r;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const uint32_t lw = lo8[p >> 1], b = (2 * p) & 3;
+        const uint32_t v0 = __builtin_amdgcn_perm(hw[p], lw, 0x0504000Cu | (b << 8));          // (hi bits, lo byte, 0)
+        const uint32_t v1 = __builtin_amdgcn_perm(hw[p], lw, 0x0706000Cu | ((b + 1) << 8));
+        const float d0 = __uint_as_float(v0) - __uint_as_float(hw[p] << 16);
+        const float d1 = __uint_as_float(v1) - __uint_as_float(hw[p] & 0xFFFF0000u);
+        r[p] = __builtin_amdgcn_perm(__float_as_uint(d1), __float_as_uint(d0), 0x07060302u);   // (exact: 8 significant bits)
+    }
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+#define SPAN_OOB 0x40000000u      // a byte offset behind every buffer: the load returns zeros and costs no memory access
+
+template <int MT, int TN, int G, int WK, int EPI, bool NORM>
+__global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__restrict__ Wp, const void *__restrict__ Xv,
+                                                            const float *__restrict__ ssq_in, float eps, int N, int K,
+                                                            SjdGemmEpi ep)
+{
+    constexpr int TNE = TN * G, F = MT * TNE;             // tiles, accumulator fragments of a wave
+    // the sums meet in LDS in passes of FC fragments, of which every wave finishes FPW
+    constexpr int FPW = WK == 8 ? 1 : 4, FC = F < WK * FPW ? F : WK * FPW, NCH = (F + FC - 1) / FC;
+    __shared__ f32x4 red[WK][FC][64];
+    __shared__ float rs[MT * 16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, c = lane & 15;
+    const int KT = K / 32, NT = N / 16, groups = NT / TN;
+    const int kps = (KT + WK - 1) / WK;
+    const int kt0 = min(KT, wave * kps), klen = min(KT, kt0 + kps) - kt0;
+    // workgroups start their walk at different k-steps (as in the skinny kernel)
+    const int rot = klen >= 16 ? (int)((((blockIdx.x >> 3) & 31u) * (unsigned)klen) >> 5) : 0;
+
+    f32x4 acc[MT][TNE];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int t = 0; t < TNE; ++t) acc[mt][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    // Both operands through buffer descriptors: scalar offsets, one vector register of addresses for each.
+    const int g0 = blockIdx.x * G, gv = min(G, groups - g0);
+    const uint32_t gstride = (uint32_t)(KT * TN) << 10, lo_base = (uint32_t)act24_lo_base(KT);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t *>(Wp) + (size_t)g0 * KT * TN * 512, 0, gstride * gv, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(Xv), 0,
+                                                                        lo_base + ((uint32_t)(SJD_MTILES * KT) << 9), 0x00020000);
+    uint32_t goff[G];                                     // (a group behind the last one: the last one again, not written)
+#pragma unroll
+    for (int j = 0; j < G; ++j) goff[j] = gstride * min(j, gv - 1);
+
+    // sum(x^2) of every token from the partial sums its writer left: TPT threads a token, requested before the first tiles
+    // (loads return in order) and added up while those are on their way
+    constexpr int TPT = pow2_floor(4 * WK / MT), PJ = 64 / TPT;
+    const int NQ = ssq_stride(K) / 4, tok = threadIdx.x / TPT, sl = threadIdx.x % TPT;
+    const SJD_GLOBAL f32x4 *pp = as_global(reinterpret_cast<const f32x4 *>(ssq_in)) + (size_t)min(tok, MT * 16 - 1) * NQ;
+    f32x4 pr[NORM ? PJ : 1];
+    if constexpr (NORM) {
+#pragma unroll
+        for (int j = 0; j < PJ; ++j) pr[j] = pp[min(sl + j * TPT, NQ - 1)];     // (past the row's end: a duplicate, dropped below)
+    }
+
+    // Up to two row tiles: two sets of activation tiles, the next one requested with the next weights.  More: one set,
+    // each tile requested again when its products are issued (MT - 1 tiles' products ahead of its next use).
+    constexpr int AB = MT <= 2 ? 2 : 1;
+    bf16x8 w[2][TNE], h[AB][MT];
+    u32x2_t l[AB][MT];
+    auto kpos = [&](int i) {
+        const int r = i + rot, kq = kt0 + (r >= klen ? r - klen : r);
+        return (uint32_t)min(kq, KT - 1);                 // (offsets stay inside the buffers also where the walk has ended)
+    };
+    auto load_w = [&](bf16x8 (&d)[TNE], uint32_t kq, uint32_t oob) {
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+                d[j * TN + tn] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                    wr, lane * 16 + oob, goff[j] + ((kq * TN + tn) << 10), 2));         // (2: non-temporal)
+    };
+    auto load_a = [&](int b, int mt, uint32_t kq, uint32_t oob) {
+        const uint32_t tix = mt * KT + kq;
+        h[b][mt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(xr, lane * 16 + oob, tix << 10, 0));
+        l[b][mt] = __builtin_amdgcn_raw_buffer_load_b64(xr, lane * 8 + oob, lo_base + (tix << 9), 0);
+    };
+    auto step = [&](int i, int cur) {
+        const uint32_t kn = kpos(i + 1), oob = i + 1 < klen ? 0u : SPAN_OOB;
+        load_w(w[cur ^ 1], kn, oob);
+        if constexpr (AB == 2) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) load_a(cur ^ 1, mt, kn, oob);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const int b = AB == 2 ? cur : 0;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const bf16x8 bh = h[b][mt], bl = lo_by_perm(h[b][mt], l[b][mt]);
+#pragma unroll
+            for (int t = 0; t < TNE; ++t) acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[cur][t], bh, acc[mt][t], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < TNE; ++t) acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[cur][t], bl, acc[mt][t], 0, 0, 0);
+            if constexpr (AB == 1) { __builtin_amdgcn_sched_barrier(0); load_a(0, mt, kn, oob); __builtin_amdgcn_sched_barrier(0); }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    {
+        const uint32_t k0 = kpos(0), oob = klen > 0 ? 0u : SPAN_OOB;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) load_a(0, mt, k0, oob);
+        load_w(w[0], k0, oob);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // what the epilogue needs of this wave's fragments besides their sums: requested here, or pass by pass where there
+    // are too many of them to hold
+    constexpr bool EARLY = NCH * FPW <= 4;
+    EpiPre pre[EARLY ? NCH : 1][FPW];
+    auto load_pre = [&](int ch, EpiPre (&p)[FPW]) {
+#pragma unroll
+        for (int i = 0; i < FPW; ++i) {
+            const int f = min(ch * FC + wave * FPW + i, F - 1);
+            preload_epilogue<EPI>(ep, N, f / TNE * 16 + c, min((int)blockIdx.x * TNE + f % TNE, NT - 1) * 16 + g * 4, p[i]);
+        }
+    };
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) load_pre(ch, pre[ch]);
+    }
+    if constexpr (NORM) {
+        float t = 0.f;
+#pragma unroll
+        for (int j = 0; j < PJ; ++j)
+            t += sl + j * TPT < NQ ? (pr[j][0] + pr[j][1]) + (pr[j][2] + pr[j][3]) : 0.f;
+        for (int i = sl + PJ * TPT; i < NQ; i += TPT) { const f32x4 v = pp[i]; t += (v[0] + v[1]) + (v[2] + v[3]); }
+#pragma unroll
+        for (int o = TPT / 2; o > 0; o >>= 1) t += __shfl_xor(t, o);
+        if (sl == 0 && tok < MT * 16) rs[tok] = rsqrtf(t / (float)K + eps);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < klen; i += 2) { step(i, 0); step(i + 1, 1); }           // (an odd walk ends with a step of zeros)
+
+    // add the waves' sums in wave order
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+        if (ch) __syncthreads();
+        if constexpr (!EARLY) load_pre(ch, pre[0]);
+#pragma unroll
+        for (int i = 0; i < FC; ++i)
+            if (ch * FC + i < F) red[wave][i][lane] = acc[(ch * FC + i) / TNE][(ch * FC + i) % TNE];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < FPW; ++i) {
+            const int fi = wave * FPW + i, f = ch * FC + fi, tile = blockIdx.x * TNE + f % TNE;
+            if (fi < FC && f < F && tile < NT) {
+                f32x4 v = red[0][fi][lane];
+#pragma unroll
+                for (int k = 1; k < WK; ++k) v += red[k][fi][lane];
+                const int m = f / TNE * 16 + c;
+                if constexpr (NORM) v *= rs[m];
+                apply_epilogue<EPI>(ep, N, m, tile * 16 + g * 4, v, pre[EARLY ? ch : 0][i]);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// launch
+// ---------------------------------------------------------------------------------------------
+template <int MT, int TN, int G>
+static int launch_span_t(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, const SjdGemmEpi &ep, hipStream_t s)
+{
+    constexpr int WK = MT * TN * G <= 24 ? 8 : 4;         // (eight waves of 256 registers or four of 512)
+    const int NT = lin->N / 16;
+    const dim3 grid((NT + TN * G - 1) / (TN * G)), block(64 * WK);
+    const bf16_t *W = (const bf16_t *)lin->w;
+#define GO(EPI, NORM) SJD_LAUNCH((gemm_span_kernel<MT, TN, G, WK, EPI, NORM>), grid, block, 0, s, W, act, ssq_in, eps, lin->N, lin->K, ep)
+    if (ssq_in) {
+        switch (ep.kind) {
+            case SJD_EPI_STORE: GO(SJD_EPI_STORE, true); break;
+            case SJD_EPI_SILU: GO(SJD_EPI_SILU, true); break;
+            case SJD_EPI_QKV: GO(SJD_EPI_QKV, true); break;
+            default: return SJD_EINVAL;
+        }
+    } else {
+        switch (ep.kind) {
+            case SJD_EPI_STORE: GO(SJD_EPI_STORE, false); break;
+            case SJD_EPI_RESID: GO(SJD_EPI_RESID, false); break;
+            default: return SJD_EINVAL;
+        }
+    }
+#undef GO
+    HIP_TRY(hipGetLastError());
+    return SJD_OK;
+}
+
+// packed weight groups per workgroup: one workgroup per CU where six tiles a workgroup allow it (eight waves hold the sums of
+// 24 fragments and two k-steps of operands in 256 registers each, four waves 48 in 512)
+static int span_groups(const SjdLinear *lin)
+{
+    const int groups = lin->N / 16 / lin->tn;
+    return std::max(1, std::min((groups + 255) / 256, 6 / lin->tn > 3 ? 3 : 6 / lin->tn));
+}
+
+// Which projections come here.  Up to 32 rows: those that leave the skinny kernel with two or more workgroups per CU (7B
+// gate/up above; the LM head of the 775M model 10.5 -> 10.7 us alone at 16 rows, 13.4 -> 12.0 at 32).  More rows: the
+// alternative is the wide kernel, which reads the activations once for eight tiles but pays a second kernel (4-5 us) and the
+// slices' traffic.  With three tiles or more per workgroup reading all activations is the smaller price (7B QKV inside a forward: 64 rows
+// 28.6 us against 23.3 + 8.2, 128 rows 43.8 against 30.4 + 12.3; forwards of 64 and 128 rows 1.2 % and 1.1 % faster);
+// with fewer, as long as they are few bytes: all 775M projections but down (K = 1536; 295 KB at 64 rows, 590 at 128) gain
+// 14 % of a forward of 64 rows and 5 % of one of 121; 7B O at 64 rows (786 KB) makes its forward 1.7 % slower.
+bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
+{
+    const int groups = lin->N / 16 / lin->tn, tiles = span_groups(lin) * lin->tn;
+    if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4;
+    const int64_t act = (int64_t)((rows + 15) / 16 * 16) * lin->K * 3;
+    return tiles >= 3 || act <= 600 * 1024;
+}
+
+int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
+                         const SjdGemmEpi &ep, hipStream_t s)
+{
+    if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn < 1 || lin->tn > 3 || lin->N % (16 * lin->tn) || lin->K % 32) return SJD_EINVAL;
+    if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
+    const int tn = lin->tn, g = span_groups(lin);
+    int mt = (rows + 15) / 16;
+    if (mt > 4) mt = (mt + 1) & ~1;                       // variants for 16, 32, 48, 64, 96 and 128 rows
+#define CASE(MT, TN, G) if (mt == MT && tn == TN && g == G) return launch_span_t<MT, TN, G>(lin, act, ssq_in, eps, ep, s)
+#define ROWS(TN, G) CASE(1, TN, G); CASE(2, TN, G); CASE(3, TN, G); CASE(4, TN, G); CASE(6, TN, G); CASE(8, TN, G)
+    ROWS(1, 1); ROWS(1, 2); ROWS(1, 3);
+    ROWS(2, 1); ROWS(2, 2); ROWS(2, 3);
+    ROWS(3, 1); ROWS(3, 2);
+#undef ROWS
+#undef CASE
+    return SJD_EINVAL;
+}

@@ -9,7 +9,6 @@
 #define SJD_ROWS_MAX SJD_MAX_ROWS       // rows (window slots of all streams, or a prefill chunk) one forward pass handles
 #define SJD_MTILES (SJD_ROWS_MAX / 16)  // 16-row tiles of an activation matrix
 #define SJD_ROWS_SKINNY 32              // up to here the skinny projection kernel runs, above it the wide one
-#define SJD_LO16_FROM_ROWS 33           // forwards with at least this many rows keep the 2-byte lo plane (see sjd_api.hip)
 #define SJD_ROWS_F32 32                 // fp32 models (launch-bound toys): rows per forward, largest window
 
 typedef unsigned short bf16_t;  // raw bf16 bit pattern
@@ -145,7 +144,7 @@ __host__ __device__ __forceinline__ size_t act24_idx(int m, int k, int KT)
     return (((size_t)(m >> 4) * KT + (k >> 5)) << 9) + ((((k & 31) >> 3) * 16 + (m & 15)) << 3) + (k & 7);
 }
 __host__ __device__ __forceinline__ size_t act24_lo_base(int KT) { return (size_t)(SJD_MTILES * KT + 1) * 1024; }   // bytes
-// Forwards of more than SJD_ROWS_SKINNY rows (the wide projection kernel) keep the second operand ready
+// Buffers that the wide projection kernel reads (sjd_gemm_form) keep the second operand ready
 // made: the lo plane then holds bf16(value - hi) (exact: 8 significant bits), 2 bytes per value in the
 // same index order, so that a tile of either plane goes from L2 straight into LDS.  Same numbers, 4
 // bytes per value instead of 3.  A buffer is allocated for the larger form.
@@ -227,7 +226,6 @@ struct SjdLinear {
     int32_t u;        // bf16: k-steps per prefetch stage (0 = chosen at launch)
     int32_t wg, wks;  // bf16, wide kernel (more than 32 rows): weight groups per wave, K-slices (0 = chosen at launch)
     int32_t wide_from;   // bf16: rows from which the wide kernel runs (0 = above SJD_ROWS_SKINNY)
-    int32_t whole_k_rows;   // bf16: from 17 up to this many rows (at most 32) the wide kernel's whole-K variant runs (0 = never)
 };
 
 // what the bf16 GEMM does with its final fp32 values
@@ -245,7 +243,7 @@ struct SjdGemmEpi {
     const bf16_t *gain_next;     // RESID: [N] gain of the normalisation that follows
     float *ssq_out;              // RESID: [rows][ssq_stride(N)] sum of squares of the updated rows per 16 features
     void *ffn; int32_t F;                                         // SILU: [rows][F] in act24 planes
-    int32_t lo16;                // RESID, SILU: the planes they write carry the 2-byte lo plane (wide forwards)
+    int32_t lo16;                // RESID, SILU: the planes they write carry the 2-byte lo plane (their reader is the wide kernel)
     float *qact; const float *cosT, *sinT;                        // QKV
     int32_t d, hd, nblk, rows_valid, max_seq;                     // rows_valid: rows per stream whose K/V are stored
 };
@@ -344,7 +342,7 @@ struct sjd_kv {
 // bf16 models: `rows` rows per stream, stream s from ids[s] (device ids; from row id_rows on all streams share
 // emb_rows), written at row s << sm.shift.  fp32 models: one stream, ids[0].
 // err[s] (device, may be NULL): receives SJD_DEVERR_TOKEN_ID when an id of stream s lies outside the vocabulary
-// lo16: x24 gets the 2-byte lo plane (the forward runs on the wide projection kernel)
+// lo16: x24 gets the 2-byte lo plane (the first QKV projection runs on the wide kernel)
 int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, int32_t id_rows, const float *emb_rows,
                      int32_t rows, const SjdStreams &sm, float *x, void *x24, float *ssq, int32_t *const *err, bool lo16, hipStream_t s);
 int sjd_launch_rmsnorm(const sjd_model *m, float *x, const float *part, int32_t n_part, size_t part_stride,
@@ -372,8 +370,11 @@ int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const 
                          const SjdGemmEpi &ep, float *part, size_t part_elems, hipStream_t s);
 int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
                          const SjdGemmEpi &ep, float *part, size_t part_elems, hipStream_t s);
-int sjd_launch_gemm_wide3(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
-                          const SjdGemmEpi &ep, hipStream_t s);
+int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
+                         const SjdGemmEpi &ep, hipStream_t s);
+bool sjd_span_takes(const SjdLinear *lin, int32_t rows);
+// the form in which a projection over `rows` rows wants its activations: what their producer writes
+int sjd_gemm_form(const SjdLinear *lin, int32_t rows);
 void sjd_wide_plan(const SjdLinear *lin, int mt, size_t part_elems, int *g_out, int *ks_out, int *kps_out);
 size_t sjd_wide_part_elems(const SjdLinear *lin);
 int sjd_gemm_wide_setup();

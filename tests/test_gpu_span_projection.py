@@ -1,0 +1,53 @@
+"""The span projection kernel at the edges of how its launches are cut (GPU only).
+
+The check and its tolerance are those of test_gpu_forward.test_gemm_against_fp64: sampled outputs, one by one, against
+fp64 dot products, 2e-5 * sqrt(K / 128).  Whole outputs are also held to 3e-7 of 64 bits in the 2-norm: chains of 32
+k-steps of fp32 sums are 2.8e-7 away, of 64 k-steps 4e-7.
+"""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import test_gpu_forward as forward  # noqa: E402
+from test_gpu_forward import B          # noqa: E402,F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+# N -> (tiles per packed group, groups per workgroup, groups in the last workgroup)
+SHAPES = [
+    (1536, 1536),     # 1, 1
+    (4272, 1056),     # 1, 2: 267 groups, one in the last workgroup
+    (12336, 416),     # 1, 3: 771 groups in 257 workgroups
+    (6528, 1056),     # 2, 1; 33 k-steps: an odd walk, the last wave's shorter
+    (16384, 96),      # 2, 2; 3 k-steps: waves without any
+    (22048, 160),     # 2, 3: 689 groups, two in the last workgroup
+    (12288, 288),     # 3, 1; 9 k-steps: two each, one for the fifth wave, none behind it
+    (24576, 64),      # 3, 2
+]
+
+
+@pytest.mark.parametrize("N,K", SHAPES)
+@pytest.mark.parametrize("M", [33, 48, 49, 64, 65, 96, 97, 128])
+def test_spans_above_32_rows(B, M, N, K):        # noqa: F811
+    forward.test_gemm_against_fp64(B, 2, M, N, K)
+
+
+@pytest.mark.parametrize("N,K", [(22016, 4096), (22048, 160), (16384, 1536)])
+@pytest.mark.parametrize("M", [1, 16, 17, 32])
+def test_spans_up_to_32_rows(B, M, N, K):        # noqa: F811
+    forward.test_gemm_against_fp64(B, 2, M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 22016, 4096), (32, 22016, 4096), (64, 22016, 4096), (96, 22016, 4096),
+                                   (64, 12288, 4096), (64, 4608, 1536), (128, 8192, 1536)])
+def test_span_precision(B, M, N, K):        # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(N + M)
+    A = torch.randn((M, K), generator=g, device="cuda")
+    A = ((A.view(torch.int32) + 0x7F) & -256).view(torch.float32)           # 16 significant bits, as the kernel takes them
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+    C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    B.sjd_gemm_test(2, A, W.view(torch.int16), M, N, K, C)
+    ref = A.double() @ W.double().T
+    rel = float((C.double() - ref).norm() / ref.norm())
+    forward._say(f"{M} x {N} x {K}: {rel:.3e} from 64 bits")
+    assert rel < 3.0e-7
