@@ -1,7 +1,6 @@
-// Pieces shared by the two bf16 projection kernels (the skinny one for up to 32 rows and the wide one for
-// up to 128): MFMA operand types, the hi / lo split, and the epilogues that see final fp32 sums (plain
+// Pieces shared by the bf16 projection kernels (skinny, span and wide): MFMA operand types, the hi / lo split, and the epilogues that see final fp32 sums (plain
 // store, residual add + operands of the next normalisation, SiLU(gate) * up, RoPE + KV-cache write;
-// paper Sec. 4.1 Step 2).  Included by those two files only.
+// paper Sec. 4.1 Step 2).  Included by those files only.
 #pragma once
 #include "sjd_internal.h"
 
@@ -60,28 +59,43 @@ struct EpiPre {
     SJD_GLOBAL bf16_t *cache; // QKV: this layer of the stream's cache (NULL: the row belongs to no stream)
 };
 
-template <int EPI>
-__device__ __forceinline__ void preload_epilogue(const SjdGemmEpi &ep, int N, int m, int n0, EpiPre &pre)
+// ... of NF fragments (row m[i], features n0[i] .. + 3 of this lane)
+template <int EPI, int NF>
+__device__ __forceinline__ void preload_epilogue(const SjdGemmEpi &ep, int N, const int (&m)[NF], const int (&n0)[NF], EpiPre (&pre)[NF])
 {
     if (EPI == SJD_EPI_RESID) {
-        pre.x = *reinterpret_cast<const f32x4 *>(ep.out + act_off(m, n0, N / 32));
-        pre.gn = ep.out24 ? *reinterpret_cast<const uint2 *>(ep.gain_next + n0) : make_uint2(0u, 0u);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            pre[f].x = *reinterpret_cast<const f32x4 *>(ep.out + act_off(m[f], n0[f], N / 32));
+            pre[f].gn = ep.out24 ? *reinterpret_cast<const uint2 *>(ep.gain_next + n0[f]) : make_uint2(0u, 0u);
+        }
     } else if (EPI == SJD_EPI_QKV) {
         const int half = ep.hd >> 1;
+        int n_s[NF];
         // the stream that owns row m: its cache length and cache.  What this costs is round trips to memory in front of
         // the stores, so it is two scalar loads in a row whatever the number of streams (walking the table entry by entry
-        // made the 775M forward of 4 images 1576 us, now 1565).
-        const int stream = m >> ep.sm.shift;
-        pre.row = m & ((1 << ep.sm.shift) - 1);
-        int n_s = 0;
-        pre.cache = nullptr;
+        // made the 775M forward of 4 images 1576 us, now 1565), and the same two for all fragments.
+#pragma unroll
+        for (int f = 0; f < NF; ++f) { n_s[f] = 0; pre[f].cache = nullptr; pre[f].row = m[f] & ((1 << ep.sm.shift) - 1); }
         if (ep.sm.shift >= 4) {
-            // a stream owns whole 16-row tiles: one owner per wave
-            const int su = __builtin_amdgcn_readfirstlane(stream);
-            if (su < ep.sm.count) {
-                const SjdStreamEntry e = stream_entry(ep.sm, su);
-                n_s = *as_global(e.n);
-                pre.cache = as_global(e.kvc) + ep.layer_off;
+            // a stream owns whole 16-row tiles: one owner per fragment
+            if (ep.sm.count > 0) {
+                SjdStreamEntry e[NF];
+#pragma unroll
+                for (int f = 0; f < NF; ++f) e[f] = ep.sm.first;
+                if (ep.sm.count > 1) {
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        const int su = __builtin_amdgcn_readfirstlane(m[f] >> ep.sm.shift);
+                        const SJD_GLOBAL SjdStreamEntry *t = as_global(ep.sm.table) + min(su, ep.sm.count - 1);
+                        e[f].n = t->n; e[f].kvc = t->kvc;
+                    }
+                }
+#pragma unroll
+                for (int f = 0; f < NF; ++f) n_s[f] = *as_global(e[f].n);
+#pragma unroll
+                for (int f = 0; f < NF; ++f)
+                    if (m[f] >> ep.sm.shift < ep.sm.count) pre[f].cache = as_global(e[f].kvc) + ep.layer_off;
             }
         } else {
             // several owners in a tile: every entry, then every length, requested together; each lane picks its own
@@ -94,17 +108,30 @@ __device__ __forceinline__ void preload_epilogue(const SjdGemmEpi &ep, int N, in
 #pragma unroll
                 for (int i = 0; i < SJD_MAX_STREAMS; ++i) n_e[i] = *as_global(e[i].n);
 #pragma unroll
-                for (int i = 0; i < SJD_MAX_STREAMS; ++i)
-                    if (i == stream && i < ep.sm.count) { n_s = n_e[i]; pre.cache = as_global(e[i].kvc) + ep.layer_off; }
+                for (int f = 0; f < NF; ++f)
+#pragma unroll
+                    for (int i = 0; i < SJD_MAX_STREAMS; ++i)
+                        if (i == m[f] >> ep.sm.shift && i < ep.sm.count) { n_s[f] = n_e[i]; pre[f].cache = as_global(e[i].kvc) + ep.layer_off; }
             }
         }
-        pre.pos = min(n_s + pre.row, ep.max_seq - 1);   // rows past the window are computed but never stored
-        // (V fragments fetch factors they do not use: no branch around the loads)
-        const int j = ((n0 % ep.d) % ep.hd) >> 1;
-        const float2 cc = *reinterpret_cast<const float2 *>(ep.cosT + (size_t)pre.pos * half + j);
-        const float2 ss = *reinterpret_cast<const float2 *>(ep.sinT + (size_t)pre.pos * half + j);
-        pre.c0 = cc.x; pre.c1 = cc.y; pre.s0 = ss.x; pre.s1 = ss.y;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            pre[f].pos = min(n_s[f] + pre[f].row, ep.max_seq - 1);   // rows past the window are computed but never stored
+            // (V fragments fetch factors they do not use: no branch around the loads)
+            const int j = (n0[f] & (ep.hd - 1)) >> 1;        // (hd is a power of two and divides d)
+            const float2 cc = *reinterpret_cast<const float2 *>(ep.cosT + (size_t)pre[f].pos * half + j);
+            const float2 ss = *reinterpret_cast<const float2 *>(ep.sinT + (size_t)pre[f].pos * half + j);
+            pre[f].c0 = cc.x; pre[f].c1 = cc.y; pre[f].s0 = ss.x; pre[f].s1 = ss.y;
+        }
     }
+}
+template <int EPI>
+__device__ __forceinline__ void preload_epilogue(const SjdGemmEpi &ep, int N, int m, int n0, EpiPre &pre)
+{
+    const int m_[1] = {m}, n_[1] = {n0};
+    EpiPre p_[1];
+    preload_epilogue<EPI, 1>(ep, N, m_, n_, p_);
+    pre = p_[0];
 }
 
 // One accumulator fragment: lane l of the MFMA result holds features n0..n0+3 (packed order) of
@@ -139,7 +166,7 @@ __device__ __forceinline__ void apply_epilogue(const SjdGemmEpi &ep, int N, int 
             // Q or K: packed order inside a head is (j, j+half, j+1, j+1+half, ...)
             const int is_k = n0 >= d;
             const int c = n0 - (is_k ? d : 0);
-            const int head = c / hd, j = (c % hd) >> 1;
+            const int head = c >> ep.hd_shift, j = (c & (hd - 1)) >> 1;
             const float c0 = pre.c0, s0 = pre.s0, c1 = pre.c1, s1 = pre.s1;
             const float r0 = v[0] * c0 - v[1] * s0, r0p = v[1] * c0 + v[0] * s0;   // dims j, j+half
             const float r1 = v[2] * c1 - v[3] * s1, r1p = v[3] * c1 + v[2] * s1;   // dims j+1, j+1+half
@@ -161,7 +188,7 @@ __device__ __forceinline__ void apply_epilogue(const SjdGemmEpi &ep, int N, int 
         } else if (pre.row < ep.rows_valid && pre.cache) {
             // V: natural feature order
             const int col = n0 - 2 * d;
-            const int head = col / hd, dim = col % hd;
+            const int head = col >> ep.hd_shift, dim = col & (hd - 1);
             SJD_GLOBAL bf16_t *rec = pre.cache + kv_block_off(head, pos >> 5, ep.nblk, hd);
             const int kk = pos & 31;
 #pragma unroll

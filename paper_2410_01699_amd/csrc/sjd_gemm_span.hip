@@ -142,18 +142,18 @@ __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__rest
     // what the epilogue needs of this wave's fragments besides their sums: requested here, or pass by pass where there
     // are too many of them to hold
     constexpr bool EARLY = NCH * FPW <= 4;
-    EpiPre pre[EARLY ? NCH : 1][FPW];
-    auto load_pre = [&](int ch, EpiPre (&p)[FPW]) {
+    constexpr int NPRE = (EARLY ? NCH : 1) * FPW;
+    EpiPre pre[NPRE];
+    auto load_pre = [&](int ch0) {
+        int pm[NPRE], pn[NPRE];
 #pragma unroll
-        for (int i = 0; i < FPW; ++i) {
-            const int f = min(ch * FC + wave * FPW + i, F - 1);
-            preload_epilogue<EPI>(ep, N, f / TNE * 16 + c, min((int)blockIdx.x * TNE + f % TNE, NT - 1) * 16 + g * 4, p[i]);
+        for (int i = 0; i < NPRE; ++i) {
+            const int f = min((ch0 + i / FPW) * FC + wave * FPW + i % FPW, F - 1);
+            pm[i] = f / TNE * 16 + c; pn[i] = min((int)blockIdx.x * TNE + f % TNE, NT - 1) * 16 + g * 4;
         }
+        preload_epilogue<EPI, NPRE>(ep, N, pm, pn, pre);
     };
-    if constexpr (EARLY) {
-#pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) load_pre(ch, pre[ch]);
-    }
+    if constexpr (EARLY) load_pre(0);
     if constexpr (NORM) {
         float t = 0.f;
 #pragma unroll
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__rest
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         if (ch) __syncthreads();
-        if constexpr (!EARLY) load_pre(ch, pre[0]);
+        if constexpr (!EARLY) load_pre(ch);
 #pragma unroll
         for (int i = 0; i < FC; ++i)
             if (ch * FC + i < F) red[wave][i][lane] = acc[(ch * FC + i) / TNE][(ch * FC + i) % TNE];
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__rest
                 for (int k = 1; k < WK; ++k) v += red[k][fi][lane];
                 const int m = f / TNE * 16 + c;
                 if constexpr (NORM) v *= rs[m];
-                apply_epilogue<EPI>(ep, N, m, tile * 16 + g * 4, v, pre[EARLY ? ch : 0][i]);
+                apply_epilogue<EPI>(ep, N, m, tile * 16 + g * 4, v, pre[(EARLY ? ch : 0) * FPW + i]);
             }
         }
     }

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wide_kernel(const bf16_t *__r
 // planes held x * gain and ssq_in the per-16-feature sums of squares of x), and runs the epilogue.
 // Workgroup (x, mt): M-tile mt, the `ft` n tiles of column group x, one per wave; lane l of a wave holds features
 // 16 ntile + 4 (l / 16) .. + 4 of token 16 mt + l % 16, exactly as the MFMA left them.  What it costs is latency: a
-// launch, one round of loads, the stores.  So everything (up to four slices, the epilogue's operands, the sums of
+// launch, one round of loads, the stores.  So everything (up to sixteen slices, the epilogue's operands, the sums of
 // squares) is requested before anything is used, and the workgroups are cut like those of the first kernel: with both
 // grids a multiple of eight column groups wide, a group's slices and its epilogue meet in one XCD's L2.
 template <int EPI, int PRO>
@@ -186,9 +186,15 @@ __global__ __launch_bounds__(1024) void gemm_wide_epilogue_kernel(const f32x4 *_
     const int nt = blockIdx.x * ft + wave, ntile = min(nt, NT - 1);            // (past the end: the last tile, not written)
     const f32x4 *p = part + ((size_t)mt * NT + ntile) * 64 + lane;
     const size_t step = (size_t)MT * NT * 64;                     // from one slice to the next
-    f32x4 q[4];
+    f32x4 q[16];
 #pragma unroll
     for (int i = 0; i < 4; ++i) q[i] = p[(size_t)min(i, KS - 1) * step];
+#pragma unroll
+    for (int i = 4; i < 16; i += 4) {
+        if (i >= KS) break;
+#pragma unroll
+        for (int j = i; j < i + 4; ++j) q[j] = p[(size_t)min(j, KS - 1) * step];
+    }
     const int f_m = mt * 16 + c, f_n0 = ntile * 16 + g * 4;
     EpiPre pre;
     preload_epilogue<EPI>(ep, N, f_m, f_n0, pre);
@@ -211,13 +217,8 @@ __global__ __launch_bounds__(1024) void gemm_wide_epilogue_kernel(const f32x4 *_
     }
     f32x4 v = q[0];
 #pragma unroll
-    for (int i = 1; i < 4; ++i) if (i < KS) v += q[i];
-    for (int y = 4; y < KS; y += 4) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) q[i] = p[(size_t)min(y + i, KS - 1) * step];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) if (y + i < KS) v += q[i];
-    }
+    for (int i = 1; i < 16; ++i) if (i < KS) v += q[i];
+    for (int y = 16; y < KS; ++y) v += p[(size_t)y * step];
     if (PRO == SJD_PRO_NORM) v *= rs[c];
     if (nt < NT) apply_epilogue<EPI>(ep, N, f_m, f_n0, v, pre);
 }

@@ -245,7 +245,7 @@ struct SjdGemmEpi {
     void *ffn; int32_t F;                                         // SILU: [rows][F] in act24 planes
     int32_t lo16;                // RESID, SILU: the planes they write carry the 2-byte lo plane (their reader is the wide kernel)
     float *qact; const float *cosT, *sinT;                        // QKV
-    int32_t d, hd, nblk, rows_valid, max_seq;                     // rows_valid: rows per stream whose K/V are stored
+    int32_t d, hd, hd_shift, nblk, rows_valid, max_seq;           // hd = 1 << hd_shift (32, 64 or 128); rows_valid: rows per stream whose K/V are stored
 };
 
 struct SjdLayer {
