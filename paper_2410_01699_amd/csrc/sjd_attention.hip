@@ -156,7 +156,7 @@ __global__ void attn_combine_kernel(const float *__restrict__ part, int splits, 
 // the V^T tiles use the same key order, which makes the probabilities the B operand of the second
 // product without any cross-lane movement.
 //
-// attn_split_kernel: workgroup (head, split) of AW waves takes a contiguous range of blocks; wave w
+// attn_split_kernel: workgroup (head, split) of AW waves (4 or 8) takes a contiguous range of blocks; wave w
 // handles every AW-th block of it with an online softmax (running max, denominator, unnormalised
 // O^T per query); the waves are merged through LDS in wave order and the workgroup writes one
 // partial result.  attn_merge_kernel combines the splits of a head in split order.
@@ -184,22 +184,23 @@ __device__ __forceinline__ void arrive_and_wait()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-#define AW 4
 // Up to about 1000 positions a launch is one round of latencies (arguments, cache length, K and V, merge); above, what the
 // workgroups in flight can request bounds it.  Hence:
 //  - two waves per SIMD, at most 256 registers each (left alone the compiler took 316 for heads of 128 and 32 queries, one
 //    workgroup per CU): the scores of every query tile come first, so that the key tiles' registers are free before the
 //    probabilities are made (1240 positions x 2 contexts of 32 queries: 35.7 -> 27.1 us, 23.1 with what follows);
+//  - keys and values as non-temporal loads (each is read once a forward; a plain read of this chip runs at 6.4 TB/s with
+//    them and at 5.9 without): one context of 16 drafts at 3967 positions 3422 -> 3348 us, eight at 583 6400 -> 6330;
 //  - loads in the order of their use (Q, K, V; the next block's K during the probabilities), as global accesses with
 //    nothing conditional between a load and its use, so that each wait is for its own loads only; and the arguments of the
 //    first loads in registers (16 queries at 600 positions: 8.3 -> 6.7 us; 7B forward of 16 drafts there 2998 -> 2942).
 // partial record of (head, split): O[MT*16][HD] unnormalised, then m[MT*16], then l[MT*16]
-template <int HD, int MT>
+template <int HD, int MT, int AW>
 __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n0, const int32_t *done0, const bf16_t *kvc0,
                                                             const float *__restrict__ qact, int d, int nblk_cache,
                                                             int rows, int splits, int qgroups, int shift,
                                                             float *__restrict__ part, const SjdStreamEntry *table,
-                                                            size_t layer_off)
+                                                            size_t layer_off, void *__restrict__ out, int lo16)
 {
     // (n0, done0, kvc0: stream 0, its cache at this layer; they and all that every workgroup needs at once are the
     // 14 registers of arguments that arrive with the dispatch, in front of the first dependent load)
@@ -254,14 +255,14 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int pl = 0; pl < 2; ++pl) ka[h][ks][pl] = rec[((h * KS + ks) * 2 + pl) * 64];
+                for (int pl = 0; pl < 2; ++pl) ka[h][ks][pl] = __builtin_nontemporal_load(rec + ((h * KS + ks) * 2 + pl) * 64);
     };
     auto load_v = [&](int blk) {
         const SJD_GLOBAL bf16x8 *rec = reinterpret_cast<const SJD_GLOBAL bf16x8 *>(kvc + kv_block_off(head, blk, nblk_cache, HD)) + lane;
 #pragma unroll
         for (int t = 0; t < DT; ++t)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) va[t][pl] = rec[(2 * KS * 2 + t * 2 + pl) * 64];
+            for (int pl = 0; pl < 2; ++pl) va[t][pl] = __builtin_nontemporal_load(rec + (2 * KS * 2 + t * 2 + pl) * 64);
     };
     // Q as B operand, shared by the waves: entry [mt][ks][plane][lane] holds
     // Q[query c (+16 mt)][32 ks + 8 g .. +8], scaled by 1/sqrt(HD), as hi and lo bf16 planes
@@ -383,6 +384,12 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
 #pragma unroll
         for (int w = 0; w < AW; ++w) M = fmaxf(M, m_all[w][mt * 16 + c]);
         const float mine = (m_run[mt] == -INFINITY) ? 0.f : __expf(m_run[mt] - M);
+        float den = 0.f;
+#pragma unroll
+        for (int w = 0; w < AW; ++w) {
+            const float mw = m_all[w][mt * 16 + c];
+            den += (mw == -INFINITY) ? 0.f : __expf(mw - M) * l_all[w][mt * 16 + c];
+        }
         if (mt) __syncthreads();                  // o_slot is reused
 #pragma unroll
         for (int t = 0; t < DT; ++t) o_slot[wave][t][lane] = o[mt][t] * mine;
@@ -393,15 +400,15 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
 #pragma unroll
             for (int w = 1; w < AW; ++w) v += o_slot[w][t][l];
             // lane l holds dims 16 t + 4 (l/16) .. +4 of query l%16
-            *reinterpret_cast<f32x4 *>(dst + (size_t)(mt * 16 + (l & 15)) * HD + t * 16 + (l >> 4) * 4) = v;
-        }
-        if (wave == 0 && g == 0) {
-            float den = 0.f;
-#pragma unroll
-            for (int w = 0; w < AW; ++w) {
-                const float mw = m_all[w][mt * 16 + c];
-                den += (mw == -INFINITY) ? 0.f : __expf(mw - M) * l_all[w][mt * 16 + c];
+            if (splits > 1) {
+                *reinterpret_cast<f32x4 *>(dst + (size_t)(mt * 16 + (l & 15)) * HD + t * 16 + (l >> 4) * 4) = v;
+            } else if (qbase + mt * 16 + c < rows) {
+                // all keys were this workgroup's: what the merge kernel would do with the only record
+                const f32x4 y = v * (1.0f / den);
+                act24_store4(out, row0 + mt * 16 + c, head * HD + t * 16 + (l >> 4) * 4, d / 32, y[0], y[1], y[2], y[3], lo16 != 0);
             }
+        }
+        if (splits > 1 && wave == 0 && g == 0) {
             dst[MT * 16 * HD + mt * 16 + c] = M;
             dst[MT * 16 * HD + MT * 16 + mt * 16 + c] = den;
         }
@@ -506,9 +513,10 @@ static int launch_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows,
 // Without and with it, 7B forwards over 3967 positions: two contexts of 16 drafts 16 splits (two rounds) 4820 us, 8 splits
 // 4757; of 32 drafts 5780 and 5713; five of 16 6 and 3 splits 8858 and 8698; eight 4 and 2 splits 11750 and 11646; six keep
 // their 5 (two rounds; 2 splits, one round, 9571 us, 5 splits 9518).  At 1239 positions two of 32: 4761 and 4702.
+static int most_splits(int pairs, int att_splits) { return pairs <= 2 ? att_splits : std::max(1, 2 * att_splits / pairs); }
 static int key_splits(int hd, int heads, int pairs, int att_splits)
 {
-    const int most = pairs <= 2 ? att_splits : std::max(1, 2 * att_splits / pairs);
+    const int most = most_splits(pairs, att_splits);
     if (hd != 128) return most;
     int best = 1, best_rounds = (heads * pairs + 511) / 512;
     for (int s = 2; s <= most; ++s) {
@@ -518,6 +526,17 @@ static int key_splits(int hd, int heads, int pairs, int att_splits)
     return best;
 }
 
+// Workgroups of eight waves instead of four, one per CU instead of two: as many waves and half as many records, which cost a
+// launch 4-6 us at its end where they are 4-8 MB, and none where one workgroup has all keys of a head (then it writes the
+// operand planes itself and no merge kernel runs).  Only where such workgroups cover the 256 CUs exactly: with three, five, six or
+// seven pairs of 32 heads they would leave CUs idle or need a second round, and nothing overlaps a round's start.  Four waves
+// and eight, us a forward: one context of 32 drafts at 1239 positions 3422 -> 3391, two 4344 -> 4288, eight of 16 at 583
+// (one split) 6330 -> 6200, prompt of 64 3998 -> 3937, one of 16 at 3967 3348 -> 3326, at 583 2778 -> 2780.
+static bool eight_waves(int hd, int heads, int pairs, int att_splits)
+{
+    return hd == 128 && 256 % (heads * pairs) == 0 && 256 / (heads * pairs) <= most_splits(pairs, att_splits);
+}
+
 template <int HD, int MT>
 static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, const SjdStreams &sm, bool lo16,
                          hipStream_t s)
@@ -525,12 +544,17 @@ static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t 
     const int d = m->cfg.d_model, H = m->cfg.n_heads;
     const size_t off = (size_t)layer * kv->k_layer_stride;
     const int qgroups = (rows + MT * 16 - 1) / (MT * 16), pairs = sm.count * qgroups;
-    const int splits = key_splits(HD, H, pairs, kv->att_splits);
+    const bool eight = eight_waves(HD, H, pairs, kv->att_splits);
+    const int splits = eight ? 256 / (H * pairs) : key_splits(HD, H, pairs, kv->att_splits);
     if (pairs * splits > 2 * std::max(kv->att_splits, SJD_MAX_STREAMS / 2)) return SJD_EINVAL;    // (what att_part holds)
     const int grows = std::min(rows, MT * 16);
-    SJD_LAUNCH((attn_split_kernel<HD, MT>), dim3(H, splits, pairs), dim3(64 * AW), 0, s, sm.first.n, sm.first.done,
-                       sm.first.kvc + off, kv->qact, d, kv->nblk, rows, splits, qgroups, sm.shift, kv->att_part, sm.table, off);
+#define GO(W) SJD_LAUNCH((attn_split_kernel<HD, MT, W>), dim3(H, splits, pairs), dim3(64 * W), 0, s, sm.first.n, sm.first.done, \
+                       sm.first.kvc + off, kv->qact, d, kv->nblk, rows, splits, qgroups, sm.shift, kv->att_part, sm.table, off, \
+                       kv->att_out, lo16 ? 1 : 0)
+    if constexpr (HD == 128) { if (eight) GO(8); else GO(4); } else GO(4);
+#undef GO
     HIP_TRY(hipGetLastError());
+    if (splits == 1) return SJD_OK;               // (written in place)
     SJD_LAUNCH((attn_merge_kernel<HD, MT>), dim3(H, (grows * (HD / 4) + ATT_MERGE_THREADS - 1) / ATT_MERGE_THREADS, pairs), dim3(ATT_MERGE_THREADS), 0, s, kv->att_part,
                        splits, d, rows, kv->att_out, sm.shift, qgroups, lo16 ? 1 : 0);
     HIP_TRY(hipGetLastError());

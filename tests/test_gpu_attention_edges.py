@@ -67,3 +67,42 @@ def test_long_caches_of_several_images(B, heads, std, lengths, L):        # noqa
             B.sjd_kv_free(kv)
         B.sjd_free_model(m)
         om.close()
+
+
+# 32 heads of 128: workgroups of eight waves.  One to eight images cut their keys into 8, 4, 2 and 1 splits (one: the split
+# kernel writes the operand planes itself); one query tile and two, whole and partial; 22 blocks of 32 at most, so waves with
+# three blocks down to none.  Three images: four waves.  (Images share one long prompt, cut at different lengths.)
+@pytest.fixture(scope="module")
+def wide_heads(B):        # noqa: F811
+    shape = synth.ModelShape(1, 4096, 32, 512, 512, 256, 512, 1280, synth.DTYPE_BF16)
+    blob = synth.make_weights(shape, seed=9, std=0.036, threads=16)
+    lengths = [697, 640, 511, 333, 100, 64, 33, 2]
+    prompt = synth.random_tokens(lengths[0], 0, 256, seed=1)
+    om = oracle.Model(shape, blob)
+    m = B.sjd_init_model(B.config_from_shape(shape), blob)
+    kvs = [B.sjd_kv_create(m) for _ in lengths]
+    q = torch.empty(shape.v_s, dtype=torch.float32, device="cuda")
+    for kv, n in zip(kvs, lengths):
+        B.sjd_prefill(m, kv, prompt[:n], None, B.sjd_sampler(8, 1.0), B.sjd_init(0, 0, -1), q)
+    yield shape, om, m, kvs, lengths, prompt
+    for kv in kvs:
+        B.sjd_kv_free(kv)
+    B.sjd_free_model(m)
+    om.close()
+
+
+@pytest.mark.parametrize("images,L", [(1, 16), (1, 31), (2, 20), (3, 16), (4, 13), (4, 32), (8, 16), (8, 5)])
+def test_heads_of_eight_waves(B, wide_heads, images, L):        # noqa: F811
+    shape, om, m, kvs, lengths, prompt = wide_heads
+    toks = np.stack([synth.random_tokens(L, 256, 512, seed=20 + b) for b in range(images)])
+    out = torch.empty((images, L, shape.v_s), dtype=torch.float32, device="cuda")
+    B.sjd_forward_logits_batch(m, kvs[:images], forward._dev(toks), L, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    om.prefill(prompt)
+    for b, n in enumerate(lengths[:images]):
+        ref = om.forward_tokens(n, toks[b])
+        err = float(np.max(np.abs(got[b] - ref)))
+        rel = float(np.linalg.norm(got[b] - ref) / np.linalg.norm(ref))
+        forward._say(f"image over {n} positions, {images} x {L}: {err:.3e}, 2-norm {rel:.3e}")
+        assert err < forward.TOL_BF16 and rel < REL, (n, err, rel)
