@@ -293,6 +293,8 @@ int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_t M, int32_
  * 3-byte form the model's projections read).  `tn` = output tiles
  * per workgroup (1..3), wk = waves splitting K (8 or 4; 0 = the choice the model makes), u = k-steps per
  * prefetch stage (2; 4 for wk = 4, M <= 16; 0 = the choice the model makes).
+ * wk >= 200: the span kernel with K cut into wk - 200 slices whose sums meet in one launch, u one-tile groups per workgroup
+ * (u = 2 with up to 8 slices, 8 with up to 8 slices and 32 rows, 4 with up to 4 at 33 .. 64 rows; tn = 1).
  * wk = u = 0 runs the kernel that the model would: for large N (two or more workgroups per CU otherwise), and above
  * 32 rows for most shapes, the span kernel (one workgroup per CU owns its features for the whole reduction).
  * More than 32 rows otherwise run the wide kernel (waves split N and share the activations through LDS, K split

@@ -153,11 +153,7 @@ extern "C" int sjd_init_model(const sjd_config *cfg, const void *host_weights, s
         off += 2 * f * d;
         rc = linear(off, (int)d, (int)f, 0, &L->down); if (rc) return fail(rc);
         off += d * f;
-        // From 17 rows on the skinny kernel reads two M-tiles of activations per weight tile in every wave; a
-        // projection with one weight tile per workgroup and a long reduction (the 7B down projection: 256
-        // workgroups, each re-reading 32 x 11008 activations) is then faster on the wide kernel, whose waves
-        // share the activations through LDS (measured alone on cold weights: 23.6 against 29.9 us).
-        if (cfg->dtype == 1 && L->down.tn == 1 && L->down.N >= 4096 && L->down.K >= 2 * L->down.N) L->down.wide_from = 17;
+        L->o.resid = L->down.resid = 1;
     }
     m->gf = plain(off, d); if (!m->gf) return fail(SJD_EHIP);
     off += d;
@@ -188,7 +184,7 @@ extern "C" int sjd_init_model(const sjd_config *cfg, const void *host_weights, s
 extern "C" void sjd_kv_free(sjd_kv *kv)
 {
     if (!kv) return;
-    void *ptrs[] = {kv->k, kv->v, kv->k_u, kv->v_u, kv->logits_last, kv->ring, kv->cfg_tab, kv->btab, kv->tokens, kv->state, kv->x, kv->x24, kv->ssq, kv->h, kv->part, kv->qact, kv->att_part, kv->att_out,
+    void *ptrs[] = {kv->k, kv->v, kv->k_u, kv->v_u, kv->logits_last, kv->ring, kv->cfg_tab, kv->btab, kv->tokens, kv->state, kv->x, kv->x24, kv->ssq, kv->h, kv->part, kv->tickets, kv->qact, kv->att_part, kv->att_out,
                     kv->ffn, kv->logits, kv->q, kv->tok_smp, kv->tok_res, kv->acc_flag, kv->draft_snap, kv->snap,
                     kv->forced, kv->ids_stage, kv->emb_stage, kv->g_draft, kv->g_p, kv->g_nacc, kv->q_first};
     for (void *p : ptrs) if (p) (void)hipFree(p);
@@ -242,11 +238,12 @@ extern "C" int sjd_kv_create(const sjd_model *m, sjd_kv **out)
     // K-slices, as many of them as any linear layer is cut into at any row count
     if (c.dtype == 1) {
         kv->part_elems = 0;
-        auto upd_wide = [&](const SjdLinear &l) { kv->part_elems = std::max(kv->part_elems, sjd_wide_part_elems(&l)); };
+        auto upd_wide = [&](const SjdLinear &l) { kv->part_elems = std::max({kv->part_elems, sjd_wide_part_elems(&l), sjd_sliced_elems(&l)}); };
         for (int l = 0; l < c.n_layers; ++l) { upd_wide(m->layers[l].qkv); upd_wide(m->layers[l].o); upd_wide(m->layers[l].gu); upd_wide(m->layers[l].down); }
         upd_wide(m->lm);
     }
     A(kv->part, kv->part_elems * 4);
+    A(kv->tickets, SJD_TICKETS * 4);
     A(kv->qact, R * d * 4);
     A(kv->att_part, sjd_attention_part_elems(m) * 4);
     A(kv->att_out, R * d * 4 + 2048);
@@ -499,6 +496,7 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     e_res.kind = SJD_EPI_RESID; e_res.out = kv->x; e_res.out24 = kv->x24; e_res.ssq_out = kv->ssq;
     e_silu.kind = SJD_EPI_SILU; e_silu.ffn = kv->ffn; e_silu.F = F;
     e_lm.kind = SJD_EPI_STORE; e_lm.out = logits; e_lm.rows_out = grows;
+    const SjdPartials part = {kv->part, kv->part_elems, kv->tickets};
     const void *x = kv->x24, *att = kv->att_out, *ffn = kv->ffn;     // hi / lo planes, 3 bytes per value
     // x24 holds x * (gain of the normalisation the next projection sits behind), kv->ssq its partial
     // sums of squares: written by the embedding kernel for the first layer, by each residual epilogue
@@ -508,16 +506,16 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
         const SjdLayer &L = m->layers[l];
         const SjdLinear &next = l + 1 < m->cfg.n_layers ? m->layers[l + 1].qkv : m->lm;
         e_qkv.layer_off = (size_t)l * kv->k_layer_stride;
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.qkv), sjd_launch_gemm_bf16(&L.qkv, x, form(L.qkv), ssq, eps, grows, e_qkv, kv->part, kv->part_elems, s));
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.qkv), sjd_launch_gemm_bf16(&L.qkv, x, form(L.qkv), ssq, eps, grows, e_qkv, part, s));
         PROF(kv, SJD_PROF_ATTENTION, kv_bytes_layer, sjd_launch_attention(m, kv, l, rows, sm, lo16(L.o), s));
         e_res.gain_next = (const bf16_t *)L.g2; e_res.lo16 = lo16(L.gu);
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm_bf16(&L.o, att, form(L.o), nullptr, 0.f, grows, e_res, kv->part, kv->part_elems, s));
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm_bf16(&L.o, att, form(L.o), nullptr, 0.f, grows, e_res, part, s));
         e_silu.lo16 = lo16(L.down);
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.gu), sjd_launch_gemm_bf16(&L.gu, x, form(L.gu), ssq, eps, grows, e_silu, kv->part, kv->part_elems, s));
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.gu), sjd_launch_gemm_bf16(&L.gu, x, form(L.gu), ssq, eps, grows, e_silu, part, s));
         e_res.gain_next = (const bf16_t *)(l + 1 < m->cfg.n_layers ? m->layers[l + 1].g1 : m->gf); e_res.lo16 = lo16(next);
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.down), sjd_launch_gemm_bf16(&L.down, ffn, form(L.down), nullptr, 0.f, grows, e_res, kv->part, kv->part_elems, s));
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.down), sjd_launch_gemm_bf16(&L.down, ffn, form(L.down), nullptr, 0.f, grows, e_res, part, s));
     }
-    PROF(kv, SJD_PROF_GEMM, lin_bytes(m, m->lm), sjd_launch_gemm_bf16(&m->lm, x, form(m->lm), ssq, eps, grows, e_lm, kv->part, kv->part_elems, s));
+    PROF(kv, SJD_PROF_GEMM, lin_bytes(m, m->lm), sjd_launch_gemm_bf16(&m->lm, x, form(m->lm), ssq, eps, grows, e_lm, part, s));
     return SJD_OK;
 }
 
@@ -1382,8 +1380,8 @@ extern "C" int sjd_dist(const float *logits, int32_t rows, int32_t V_s, const sj
 }
 
 struct GemmScratch {
-    void *Ap = nullptr, *Wp = nullptr, *part = nullptr; float *out = nullptr;
-    ~GemmScratch() { for (void *p : {Ap, Wp, part, (void *)out}) if (p) (void)hipFree(p); }
+    void *Ap = nullptr, *Wp = nullptr, *part = nullptr, *tickets = nullptr; float *out = nullptr;
+    ~GemmScratch() { for (void *p : {Ap, Wp, part, tickets, (void *)out}) if (p) (void)hipFree(p); }
 };
 
 extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_t M, int32_t N, int32_t K, float *C,
@@ -1398,7 +1396,7 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
     SjdLinear lin;
     memset(&lin, 0, sizeof(lin));
     lin.N = N; lin.K = K; lin.tn = 1; lin.w = W;
-    if (dtype >= 1) sjd_choose_tiles(&lin);
+    if (dtype >= 1) { sjd_choose_tiles(&lin); lin.resid = 1; }
     // bf16: operand planes in the form the kernel of this shape and row count reads (bf16 values are exact in either);
     // bf16 activations on the skinny kernel as fp32, split on the fly
     int form = dtype >= 1 ? sjd_gemm_form(&lin, M) : SJD_ACT_F32;
@@ -1407,8 +1405,9 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
     GemmScratch g;
     SJD_TRY(dev_alloc(&g.Ap, (size_t)SJD_ROWS_MAX * K * 4 + 2048));   // rows past M and the tile behind stay zero
     SJD_TRY(dev_alloc((void **)&g.out, (size_t)SJD_ROWS_MAX * N * 4));
-    const size_t part_elems = wide ? (size_t)8 * SJD_ROWS_MAX * N : 0;      // (room for up to 8 K-slices)
-    if (wide) SJD_TRY(dev_alloc(&g.part, part_elems * 4));
+    const size_t part_elems = dtype >= 1 ? (size_t)8 * SJD_ROWS_MAX * (N + 128) : 0;      // (room for up to 8 K-slices)
+    if (part_elems) SJD_TRY(dev_alloc(&g.part, part_elems * 4));
+    SJD_TRY(dev_alloc(&g.tickets, SJD_TICKETS * 4));
     if (dtype >= 1) {
         if (form == SJD_ACT_F32) SJD_TRY(sjd_bf16_rows_to_f32((const bf16_t *)A, M, K, (float *)g.Ap, s));
         else if (dtype == 1) SJD_TRY(sjd_bf16_rows_to_act24((const bf16_t *)A, M, K, g.Ap, s));
@@ -1420,7 +1419,7 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
         memset(&ep, 0, sizeof(ep));
         ep.kind = SJD_EPI_STORE; ep.out = g.out; ep.rows_out = M;
         SJD_TRY(sjd_launch_gemm_bf16(&lin, g.Ap, form, nullptr, 0.f, M, ep,
-                                     (float *)g.part, part_elems, s));
+                                     SjdPartials{(float *)g.part, part_elems, (uint32_t *)g.tickets}, s));
     } else {
         HIP_TRY(hipMemcpyAsync(g.Ap, A, (size_t)M * K * es, hipMemcpyDeviceToDevice, s));
         SJD_TRY(sjd_launch_gemm(0, &lin, g.Ap, M, g.out, nullptr, s));
@@ -1509,21 +1508,24 @@ extern "C" int sjd_gemm_bench(int32_t M, int32_t N, int32_t K, int32_t tn, int32
     const int chunks = (M + SJD_ROWS_MAX - 1) / SJD_ROWS_MAX, rows = chunks > 1 ? SJD_ROWS_MAX : M;
     // wk >= 100 asks for the wide kernel at any row count, with wk - 100 K-slices (0 = automatic) and u
     // weight groups per wave (0 = automatic)
-    const bool force_wide = wk >= 100;
+    const bool sliced = wk >= 200;
+    if (sliced) wk -= 200;
+    const bool force_wide = !sliced && wk >= 100;
     if (force_wide) wk -= 100;
     const bool wide = rows > SJD_ROWS_SKINNY || force_wide;
     // skinny kernel: u + 10 reads the activations in their 4-byte form (2-byte lo plane) instead of 3 bytes
-    int form = wide ? SJD_ACT_P4 : SJD_ACT_P3;
-    if (!wide && u >= 10) { u -= 10; form = SJD_ACT_P4; }
-    if (!wide && (u != 0 && u != 2 && u != 4)) return SJD_EINVAL;       // (0: the model's choice)
+    int form = wide && !sliced ? SJD_ACT_P4 : SJD_ACT_P3;
+    if (!wide && !sliced && u >= 10) { u -= 10; form = SJD_ACT_P4; }
+    if (!wide && !sliced && (u != 0 && u != 2 && u != 4)) return SJD_EINVAL;       // (0: the model's choice)
     const size_t wbytes = (size_t)N * K * 2;
     const int copies = cold ? (int)((((size_t)1 << 30) + wbytes - 1) / wbytes) + 1 : 1;
     GemmScratch g;
     SJD_TRY(dev_alloc(&g.Ap, (size_t)SJD_ROWS_MAX * K * 4 + 2048));
     SJD_TRY(dev_alloc(&g.Wp, wbytes * copies));
     SJD_TRY(dev_alloc((void **)&g.out, (size_t)SJD_ROWS_MAX * N * 4));
-    const size_t part_elems = wide ? (size_t)8 * SJD_ROWS_MAX * N : 0;      // (room for up to 8 K-slices)
-    if (wide) SJD_TRY(dev_alloc(&g.part, part_elems * 4));
+    const size_t part_elems = wide || sliced ? (size_t)8 * SJD_ROWS_MAX * (N + 128) : 0;      // (room for up to 8 K-slices)
+    if (part_elems) SJD_TRY(dev_alloc(&g.part, part_elems * 4));
+    SJD_TRY(dev_alloc(&g.tickets, SJD_TICKETS * 4));
     SjdLinear lin;
     memset(&lin, 0, sizeof(lin));
     lin.N = N; lin.K = K; lin.tn = tn; lin.w = g.Wp;
@@ -1539,8 +1541,9 @@ extern "C" int sjd_gemm_bench(int32_t M, int32_t N, int32_t K, int32_t tn, int32
     int rc = SJD_OK;
     auto one = [&]() {
         int r = SJD_OK;
+        if (sliced) return chunks > 1 ? SJD_EINVAL : sjd_launch_gemm_sliced(&lin, g.Ap, rows, ep, u, wk, SjdPartials{(float *)g.part, part_elems, (uint32_t *)g.tickets}, 0);
         for (int c = 0; c < chunks && r == SJD_OK; ++c)
-            r = sjd_launch_gemm_bf16(&lin, g.Ap, form, nullptr, 0.f, rows, ep, (float *)g.part, part_elems, 0);
+            r = sjd_launch_gemm_bf16(&lin, g.Ap, form, nullptr, 0.f, rows, ep, SjdPartials{(float *)g.part, part_elems, (uint32_t *)g.tickets}, 0);
         return r;
     };
     for (int i = 0; i < 3 && rc == SJD_OK; ++i) rc = one();

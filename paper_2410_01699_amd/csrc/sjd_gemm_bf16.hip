@@ -337,7 +337,7 @@ void sjd_choose_tiles(SjdLinear *lin)
             best_tn = t;
         }
     }
-    lin->tn = best_tn; lin->wk = 0; lin->u = 0; lin->wg = 0; lin->wks = 0; lin->wide_from = 0;
+    lin->tn = best_tn; lin->wk = 0; lin->u = 0; lin->wg = 0; lin->wks = 0; lin->wide_from = 0; lin->resid = 0;
 }
 
 template <int MT, int TN, int WK, int U, int PRO>
@@ -374,22 +374,26 @@ static int launch_epi(const SjdLinear *lin, const void *act, const float *ssq_in
 
 int sjd_gemm_form(const SjdLinear *lin, int32_t rows)
 {
-    if (sjd_span_takes(lin, rows)) return SJD_ACT_P3;
+    int g, ks;
+    if (sjd_sliced_plan(lin, rows, &g, &ks) || sjd_span_takes(lin, rows)) return SJD_ACT_P3;
     return rows > SJD_ROWS_SKINNY || (lin->wide_from > 0 && rows >= lin->wide_from) ? SJD_ACT_P4 : SJD_ACT_P3;
 }
 
 int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const float *ssq_in, float eps, int32_t rows,
-                         const SjdGemmEpi &ep, float *part, size_t part_elems, hipStream_t s)
+                         const SjdGemmEpi &ep, const SjdPartials &part, hipStream_t s)
 {
     const bool act24 = form != SJD_ACT_F32, lo16 = form == SJD_ACT_P4;
     if (rows < 1 || rows > SJD_ROWS_MAX || (ssq_in && !act24) || form < 0 || form > 2) return SJD_EINVAL;
+    int g, ks;
+    if (form == SJD_ACT_P3 && !lin->wk && !lin->u && !ssq_in && sjd_sliced_plan(lin, rows, &g, &ks))
+        return sjd_launch_gemm_sliced(lin, act, rows, ep, g, ks, part, s);
     if (form == SJD_ACT_P3 && !lin->wk && !lin->u && sjd_span_takes(lin, rows))
         return sjd_launch_gemm_span(lin, act, ssq_in, eps, rows, ep, s);
     // the wide kernel: above SJD_ROWS_SKINNY rows, or from lin->wide_from rows on; it reads the 4-byte planes
-    const bool wide = rows > SJD_ROWS_SKINNY || (lin->wide_from > 0 && rows >= lin->wide_from && lo16 && part);
+    const bool wide = rows > SJD_ROWS_SKINNY || (lin->wide_from > 0 && rows >= lin->wide_from && lo16 && part.sums);
     if (wide) {
         if (!lo16) return SJD_EINVAL;
-        return sjd_launch_gemm_wide(lin, act, ssq_in, eps, rows, ep, part, part_elems, s);
+        return sjd_launch_gemm_wide(lin, act, ssq_in, eps, rows, ep, part.sums, part.elems, s);
     }
     if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
     if (lin->tn < 1 || lin->N % (16 * lin->tn) || lin->K % 32) return SJD_EINVAL;

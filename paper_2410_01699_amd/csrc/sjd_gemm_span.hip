@@ -4,10 +4,12 @@
 // Like the skinny kernel, the waves of a workgroup split K, each streams its own weights and its own activation tiles
 // straight into registers (nothing is shared, so nothing is staged and no barrier stands in the loop) and the fp32 sums
 // meet once, through LDS, in wave order; the epilogue sees final values, so there are no K-slices in memory and no second
-// kernel.  Two things differ:
+// kernel.  Three things differ:
 //  - a workgroup owns G packed weight groups (up to six 16-feature tiles), so many that one workgroup per CU covers N.
 //    Every workgroup reads all M x K activations from L2; with the skinny kernel's two tiles the 7B gate/up projection had
 //    688 workgroups, 2.7 reads of the activations per CU.
+//  - K may be cut across gridDim.y workgroups as well, where all of it would make a workgroup read far more activations than
+//    weights or leave CUs without one: the slices' sums meet in the workgroup of a column that arrives last.
 //  - up to eight row tiles.  A wave's activation tiles are refilled in place as soon as their products are issued, the
 //    weights of the next k-step are requested one k-step ahead.
 //
@@ -43,22 +45,26 @@ __device__ __forceinline__ bf16x8 lo_by_perm(bf16x8 hi, u32x2_t lo8)
     return __builtin_bit_cast(bf16x8, r);
 }
 
+#define SPAN_AGENT 16             // cache policy sc1: stores go through to memory, loads come from there, whichever XCD asks
 #define SPAN_OOB 0x40000000u      // a byte offset behind every buffer: the load returns zeros and costs no memory access
 
-template <int MT, int TN, int G, int WK, int EPI, bool NORM>
+template <int MT, int TN, int G, int WK, int EPI, bool NORM, int KSM>
 __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__restrict__ Wp, const void *__restrict__ Xv,
-                                                            const float *__restrict__ ssq_in, float eps, int N, int K,
-                                                            SjdGemmEpi ep)
+                                                            const float *__restrict__ ssq_in, float eps, int N, int K, int kslice,
+                                                            float *part, uint32_t *tickets, SjdGemmEpi ep)
 {
+    constexpr bool SLICED = KSM > 1;                      // K cut across gridDim.y <= KSM workgroups
     constexpr int TNE = TN * G, F = MT * TNE;             // tiles, accumulator fragments of a wave
     // the sums meet in LDS in passes of FC fragments, of which every wave finishes FPW
     constexpr int FPW = WK == 8 ? 1 : 4, FC = F < WK * FPW ? F : WK * FPW, NCH = (F + FC - 1) / FC;
     __shared__ f32x4 red[WK][FC][64];
     __shared__ float rs[MT * 16];
+    __shared__ uint32_t arrived;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, c = lane & 15;
     const int KT = K / 32, NT = N / 16, groups = NT / TN;
-    const int kps = (KT + WK - 1) / WK;
-    const int kt0 = min(KT, wave * kps), klen = min(KT, kt0 + kps) - kt0;
+    const int s0 = SLICED ? (int)blockIdx.y * kslice : 0, s1 = SLICED ? min(KT, s0 + kslice) : KT;      // this K-slice
+    const int kps = (s1 - s0 + WK - 1) / WK;
+    const int kt0 = min(s1, s0 + wave * kps), klen = min(s1, kt0 + kps) - kt0;
     // workgroups start their walk at different k-steps (as in the skinny kernel)
     const int rot = klen >= 16 ? (int)((((blockIdx.x >> 3) & 31u) * (unsigned)klen) >> 5) : 0;
 
@@ -141,7 +147,7 @@ __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__rest
     __builtin_amdgcn_sched_barrier(0);
     // what the epilogue needs of this wave's fragments besides their sums: requested here, or pass by pass where there
     // are too many of them to hold
-    constexpr bool EARLY = NCH * FPW <= 4;
+    constexpr bool EARLY = !SLICED && NCH * FPW <= 4;
     constexpr int NPRE = (EARLY ? NCH : 1) * FPW;
     EpiPre pre[NPRE];
     auto load_pre = [&](int ch0) {
@@ -168,10 +174,11 @@ __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__rest
     for (int i = 0; i < klen; i += 2) { step(i, 0); step(i + 1, 1); }           // (an odd walk ends with a step of zeros)
 
     // add the waves' sums in wave order
+    f32x4 own[SLICED ? NCH * FPW : 1];
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         if (ch) __syncthreads();
-        if constexpr (!EARLY) load_pre(ch);
+        if constexpr (!EARLY && !SLICED) load_pre(ch);
 #pragma unroll
         for (int i = 0; i < FC; ++i)
             if (ch * FC + i < F) red[wave][i][lane] = acc[(ch * FC + i) / TNE][(ch * FC + i) % TNE];
@@ -183,11 +190,61 @@ __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__rest
                 f32x4 v = red[0][fi][lane];
 #pragma unroll
                 for (int k = 1; k < WK; ++k) v += red[k][fi][lane];
-                const int m = f / TNE * 16 + c;
-                if constexpr (NORM) v *= rs[m];
-                apply_epilogue<EPI>(ep, N, m, tile * 16 + g * 4, v, pre[(EARLY ? ch : 0) * FPW + i]);
+                if constexpr (SLICED) {
+                    own[ch * FPW + i] = v;
+                } else {
+                    const int m = f / TNE * 16 + c;
+                    if constexpr (NORM) v *= rs[m];
+                    apply_epilogue<EPI>(ep, N, m, tile * 16 + g * 4, v, pre[(EARLY ? ch : 0) * FPW + i]);
+                }
             }
         }
+    }
+    if constexpr (SLICED) {
+        // The slices' sums meet in the workgroup of a column that arrives last.  Records are written through to memory and
+        // read from there (no fence: a write-back of the XCD's L2 costs 20 us), each wave waits for its own stores, then the
+        // workgroup takes a ticket; nobody waits for anybody.  Slices are added in slice order, whoever is last.
+        constexpr int NV = NCH * FPW;
+        const int KS = gridDim.y, me = blockIdx.y;
+        const __amdgpu_buffer_rsrc_t pb = __builtin_amdgcn_make_buffer_rsrc(part + (size_t)blockIdx.x * KS * F * 256, 0, KS * F << 10, 0x00020000);
+        int vf[NV];                               // this wave's fragments (F: none)
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int fi = wave * FPW + i % FPW, f = i / FPW * FC + fi;
+            vf[i] = fi < FC && f < F && (int)blockIdx.x * TNE + f % TNE < NT ? f : F;
+            if (vf[i] < F) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, own[i]), pb, lane * 16, (me * F + f) << 10, SPAN_AGENT);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);            // this wave's records have reached memory
+        __syncthreads();
+        if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(tickets + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (arrived != (uint32_t)KS - 1) return;
+        f32x4 q[NV][KSM];
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int k = 0; k < KSM; ++k)
+                q[i][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                    pb, lane * 16 + (k < KS && k != me && vf[i] < F ? 0u : SPAN_OOB), (min(k, KS - 1) * F + min(vf[i], F - 1)) << 10, SPAN_AGENT));
+        int pm[NV], pn[NV];
+        EpiPre e[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int f = min(vf[i], F - 1);
+            pm[i] = f / TNE * 16 + c; pn[i] = min((int)blockIdx.x * TNE + f % TNE, NT - 1) * 16 + g * 4;
+        }
+        preload_epilogue<EPI, NV>(ep, N, pm, pn, e);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (vf[i] == F) continue;
+            f32x4 v = me == 0 ? own[i] : q[i][0];
+#pragma unroll
+            for (int k = 1; k < KSM; ++k) v += k == me ? own[i] : q[i][k];      // (slices behind the last one: zeros)
+            if constexpr (NORM) v *= rs[pm[i]];
+            apply_epilogue<EPI>(ep, N, pm[i], pn[i], v, e[i]);
+        }
+        if (threadIdx.x == 0) __hip_atomic_store(tickets + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -201,7 +258,7 @@ static int launch_span_t(const SjdLinear *lin, const void *act, const float *ssq
     const int NT = lin->N / 16;
     const dim3 grid((NT + TN * G - 1) / (TN * G)), block(64 * WK);
     const bf16_t *W = (const bf16_t *)lin->w;
-#define GO(EPI, NORM) SJD_LAUNCH((gemm_span_kernel<MT, TN, G, WK, EPI, NORM>), grid, block, 0, s, W, act, ssq_in, eps, lin->N, lin->K, ep)
+#define GO(EPI, NORM) SJD_LAUNCH((gemm_span_kernel<MT, TN, G, WK, EPI, NORM, 1>), grid, block, 0, s, W, act, ssq_in, eps, lin->N, lin->K, 0, (float *)nullptr, (uint32_t *)nullptr, ep)
     if (ssq_in) {
         switch (ep.kind) {
             case SJD_EPI_STORE: GO(SJD_EPI_STORE, true); break;
@@ -221,6 +278,39 @@ static int launch_span_t(const SjdLinear *lin, const void *act, const float *ssq
     return SJD_OK;
 }
 
+template <int MT, int G, int KSM>
+static int launch_sliced_t(const SjdLinear *lin, const void *act, const SjdGemmEpi &ep, int ks, const SjdPartials &part, hipStream_t s)
+{
+    const int cols = (lin->N / 16 + G - 1) / G, kps = (lin->K / 32 + ks - 1) / ks;
+    ks = (lin->K / 32 + kps - 1) / kps;
+    if (ks > KSM || cols > SJD_TICKETS || !part.sums || !part.tickets || (size_t)cols * ks * MT * G * 256 > part.elems) return SJD_EINVAL;
+#define GO(EPI) SJD_LAUNCH((gemm_span_kernel<MT, 1, G, 8, EPI, false, KSM>), dim3(cols, ks), dim3(512), 0, s, (const bf16_t *)lin->w, act, \
+                           (const float *)nullptr, 0.f, lin->N, lin->K, kps, part.sums, part.tickets, ep)
+    switch (ep.kind) {
+        case SJD_EPI_STORE: GO(SJD_EPI_STORE); break;      // (test hooks)
+        case SJD_EPI_RESID: GO(SJD_EPI_RESID); break;
+        default: return SJD_EINVAL;
+    }
+#undef GO
+    HIP_TRY(hipGetLastError());
+    return SJD_OK;
+}
+
+int sjd_launch_gemm_sliced(const SjdLinear *lin, const void *act, int32_t rows, const SjdGemmEpi &ep, int g, int ks,
+                           const SjdPartials &part, hipStream_t s)
+{
+    if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn != 1 || lin->N % 16 || lin->K % 32 || ks < 1) return SJD_EINVAL;
+    if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
+    int mt = (rows + 15) / 16;
+    if (mt > 4) mt = (mt + 1) & ~1;
+#define CASE(MT, G, KSM) if (mt == MT && g == G && ks <= KSM) return launch_sliced_t<MT, G, KSM>(lin, act, ep, ks, part, s)
+    CASE(1, 2, 8); CASE(2, 2, 8); CASE(3, 2, 8); CASE(4, 2, 8); CASE(6, 2, 8); CASE(8, 2, 8);
+    CASE(3, 4, 4); CASE(4, 4, 4);
+    CASE(1, 8, 8); CASE(2, 8, 8);
+#undef CASE
+    return SJD_EINVAL;
+}
+
 // packed weight groups per workgroup: one workgroup per CU where six tiles a workgroup allow it (eight waves hold the sums of
 // 24 fragments and two k-steps of operands in 256 registers each, four waves 48 in 512)
 static int span_groups(const SjdLinear *lin)
@@ -236,6 +326,45 @@ static int span_groups(const SjdLinear *lin)
 // 28.6 us against 23.3 + 8.2, 128 rows 43.8 against 30.4 + 12.3; forwards of 64 and 128 rows 1.2 % and 1.1 % faster);
 // with fewer, as long as they are few bytes: all 775M projections but down (K = 1536; 295 KB at 64 rows, 590 at 128) gain
 // 14 % of a forward of 64 rows and 5 % of one of 121; 7B O at 64 rows (786 KB) makes its forward 1.7 % slower.
+// Which projections are cut into K-slices here, and how: G groups of one tile a workgroup, KS slices.  O and down only (their
+// output is added to the residual stream), where a workgroup with all of K reads more activations than weights or CUs stay
+// without a workgroup:
+//  - 256 tiles and more, long K (7B down), up to 32 rows: 8 x 8 cuts the activations a workgroup reads to an eighth.  16 rows inside
+//    a forward 20.7 us (skinny kernel) -> 19.0, 32 rows 19.4 + 5.3 (wide kernel and its second) -> 21.9.  At 64 rows the last
+//    workgroup's share grows: 22 + 5.2 -> 27.9, so the wide kernel keeps those.
+//  - 256 tiles and more, other K (7B O), 33 to 64 rows: 4 x 4; forward of 2 x 32 rows 4251 -> 4202 us, prompt of 64 3880 -> 3808.
+//    At 128 rows it loses (5962 -> 5994), up to 32 the skinny kernel alone needs 8.2 and 10.8 us, sliced 9.9 and 11.1.
+//  - fewer tiles (775M, 96 of them for 256 CUs): 2 x 4.  down at 16, 64, 121 rows 8.1 -> 7.0, 7.4 + 4.1 -> 8.3, 10.1 + 5.1 -> 12.4 us, O at
+//    64 rows 8.7 -> 8.3; O up to 32 rows is faster whole (4.3 us alone against 5.0).
+bool sjd_sliced_plan(const SjdLinear *lin, int32_t rows, int *g, int *ks)
+{
+    const int tiles = lin->N / 16, KT = lin->K / 32;
+    const bool longk = lin->K >= 2 * lin->N, few = rows <= SJD_ROWS_SKINNY;
+    *g = *ks = 1;
+    if (!lin->resid || lin->tn != 1) return false;
+    if (tiles >= 256) {
+        if (longk ? !few : few || rows > 64) return false;
+        *g = *ks = longk ? 8 : 4;
+    } else {
+        if (few && !longk) return false;
+        *g = 2;
+        *ks = 512 / tiles >= 8 ? 8 : 512 / tiles >= 4 ? 4 : 2;
+    }
+    while (*ks > 1 && KT / *ks < 8) *ks /= 2;             // (a k-step for every wave)
+    return *ks > 1;
+}
+
+// floats of slices' sums of such a projection at most, over all row counts
+size_t sjd_sliced_elems(const SjdLinear *lin)
+{
+    size_t most = 0;
+    for (int rows = 16; rows <= SJD_ROWS_MAX; rows += 16) {
+        int g, ks;
+        if (sjd_sliced_plan(lin, rows, &g, &ks)) most = std::max(most, (size_t)((lin->N / 16 + g - 1) / g) * ks * (rows / 16 + 1) * g * 256);       // (row tiles in pairs)
+    }
+    return most;
+}
+
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 {
     const int groups = lin->N / 16 / lin->tn, tiles = span_groups(lin) * lin->tn;

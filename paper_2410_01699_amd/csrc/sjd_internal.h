@@ -225,6 +225,7 @@ struct SjdLinear {
     int32_t wk;       // bf16: waves per workgroup splitting K (0 = chosen at launch)
     int32_t u;        // bf16: k-steps per prefetch stage (0 = chosen at launch)
     int32_t wg, wks;  // bf16, wide kernel (more than 32 rows): weight groups per wave, K-slices (0 = chosen at launch)
+    int32_t resid;       // bf16: a projection whose output is added to the residual stream (O, down): it may be cut into K-slices
     int32_t wide_from;   // bf16: rows from which the wide kernel runs (0 = above SJD_ROWS_SKINNY)
 };
 
@@ -284,6 +285,7 @@ struct sjd_kv {
     void *h;              // fp32 models: [rows][d] normalised activations
     float *part;          // fp32 models: GEMM output
     size_t part_elems;
+    uint32_t *tickets;    // bf16 models: [SJD_TICKETS] zeroed counters of the projections cut into K-slices
     float *qact;          // [rows][d] rotated queries (fp32)
     float *att_part;      // attention partials per (head, split): [rows][hd] + m,l
     int32_t att_splits;
@@ -355,6 +357,14 @@ int sjd_launch_reduce_rows(const float *part, int32_t n_part, size_t part_stride
                            float *out, const SjdState *st, hipStream_t s);
 int sjd_launch_gemm(int32_t dtype, const SjdLinear *lin, const void *act, int32_t rows, float *part,
                     const SjdState *st, hipStream_t s);
+// scratch of the projections that cut K across workgroups: fp32 sums, and one zeroed counter per column group, which a launch
+// leaves zeroed
+#define SJD_TICKETS 1024
+struct SjdPartials { float *sums; size_t elems; uint32_t *tickets; };
+bool sjd_sliced_plan(const SjdLinear *lin, int32_t rows, int *g, int *ks);
+size_t sjd_sliced_elems(const SjdLinear *lin);
+int sjd_launch_gemm_sliced(const SjdLinear *lin, const void *act, int32_t rows, const SjdGemmEpi &ep, int g, int ks,
+                           const SjdPartials &part, hipStream_t s);
 int sjd_repack_bf16(const bf16_t *src_dev, bf16_t *dst_dev, int32_t N, int32_t K, int32_t tn, int32_t perm, int32_t d,
                     int32_t hd, hipStream_t s);
 void sjd_choose_tiles(SjdLinear *lin);
@@ -367,7 +377,7 @@ void sjd_choose_tiles(SjdLinear *lin);
 #define SJD_ACT_P3 1      // operand planes, 1-byte lo plane (3 bytes per value)
 #define SJD_ACT_P4 2      // operand planes, 2-byte lo plane (4 bytes per value)
 int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const float *ssq_in, float eps, int32_t rows,
-                         const SjdGemmEpi &ep, float *part, size_t part_elems, hipStream_t s);
+                         const SjdGemmEpi &ep, const SjdPartials &part, hipStream_t s);
 int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
                          const SjdGemmEpi &ep, float *part, size_t part_elems, hipStream_t s);
 int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,

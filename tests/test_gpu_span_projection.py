@@ -38,7 +38,45 @@ def test_spans_up_to_32_rows(B, M, N, K):        # noqa: F811
     forward.test_gemm_against_fp64(B, 2, M, N, K)
 
 
-@pytest.mark.parametrize("M,N,K", [(16, 22016, 4096), (32, 22016, 4096), (64, 22016, 4096), (96, 22016, 4096),
+# K cut into slices (tn = 1 everywhere): 8 tiles x 8 slices up to 32 rows, also with three ragged tiles and a short last
+# slice; 4 x 4 at 33 .. 64; 2 tiles x 4 slices (96 tiles), 2 x 4 with one tile in the last column, 2 x 8 (16 tiles, 8 and 9
+# k-steps a slice), 2 x 2 (16 k-steps)
+@pytest.mark.parametrize("N,K,Ms", [(4096, 11008, (1, 16, 17, 32)), (4176, 8384, (5, 16, 32)), (4096, 4096, (33, 48, 49, 64)),
+                                    (1536, 4096, (1, 16, 17, 33, 48, 64, 65, 96, 128)), (1536, 1536, (33, 64, 96, 128)),
+                                    (1040, 2112, (16, 40, 100)), (256, 2048, (16, 128)), (256, 2080, (31, 64)), (256, 512, (16, 80))])
+def test_sliced_spans(B, N, K, Ms):        # noqa: F811
+    for M in Ms:
+        forward.test_gemm_against_fp64(B, 2, M, N, K)
+
+
+# the wide kernel where nothing else goes: 7 K-slices with a short last one over a ragged column, two-tile groups
+@pytest.mark.parametrize("M,N,K", [(64, 4112, 4224), (128, 4112, 4224), (64, 8160, 4096), (96, 8160, 4096)])
+def test_wide_ragged(B, M, N, K):        # noqa: F811
+    forward.test_gemm_against_fp64(B, 2, M, N, K)
+
+
+# Whoever arrives last adds the slices, always in the same order: a forward has the same bits every time.
+@pytest.mark.parametrize("L", [16, 64])
+def test_sliced_sums_have_one_order(B, L):        # noqa: F811
+    from paper_2410_01699_amd import synth
+    shape = synth.ModelShape(2, 1536, 24, 4096, 512, 256, 512, 256, synth.DTYPE_BF16)
+    m = B.sjd_init_model(B.config_from_shape(shape), synth.make_weights(shape, seed=5, threads=16))
+    kv = B.sjd_kv_create(m)
+    try:
+        q = torch.empty(shape.v_s, dtype=torch.float32, device="cuda")
+        B.sjd_prefill(m, kv, synth.random_tokens(70, 0, 256, seed=1), None, B.sjd_sampler(8, 1.0), B.sjd_init(0, 0, -1), q)
+        toks = forward._dev(synth.random_tokens(L, 256, 512, seed=2))
+        outs = [torch.empty((L, shape.v_s), dtype=torch.float32, device="cuda") for _ in range(40)]
+        for o in outs:
+            B.sjd_forward_logits(m, kv, toks, L, o)
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all() and all(torch.equal(outs[0], o) for o in outs[1:])
+    finally:
+        B.sjd_kv_free(kv)
+        B.sjd_free_model(m)
+
+
+@pytest.mark.parametrize("M,N,K", [(16, 4096, 11008), (32, 4096, 11008), (64, 4096, 4096), (16, 1536, 4096), (128, 1536, 4096), (16, 22016, 4096), (32, 22016, 4096), (64, 22016, 4096), (96, 22016, 4096),
                                    (64, 12288, 4096), (64, 4608, 1536), (128, 8192, 1536)])
 def test_span_precision(B, M, N, K):        # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(N + M)
