@@ -33,7 +33,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(const float *
     constexpr int RPT = (ROWS + RG - 1) / RG;     // rows per thread there
     __shared__ float qs[ROWS][HD + 1];
     __shared__ float ks[ATT_TILE][HD + 1];        // reused for V
-    __shared__ float sc[ROWS][ATT_TILE];
+    __shared__ float sc[ROWS][ATT_TILE + 1];
     __shared__ float m_run[ROWS], l_run[ROWS], scale_old[ROWS];
 
     const int head = blockIdx.x, split = blockIdx.y, tid = threadIdx.x;
@@ -55,17 +55,36 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(const float *
     const int pv_j = tid % HD, pv_g = tid / HD;
     __syncthreads();
 
+    // A launch of these models is a chain of latencies: a tile's keys, then its values, are requested together (positions
+    // behind the end repeat the last one and count as zero), the rows behind the window are left out, the exponentials of a
+    // row are made by eight threads.  Their sum stays one chain in key order.  (8 rows over 88 positions: 12.8 -> 6.1 us, an 8 x 8 image 5436 -> 4776.)
+    constexpr int LPT = ATT_TILE * HD / ATT_THREADS;
     for (int t0 = k_beg; t0 < k_end; t0 += ATT_TILE) {
         const int tl = min(ATT_TILE, k_end - t0);
-        for (int e = tid; e < ATT_TILE * HD; e += ATT_THREADS) {
-            int kk = e / HD, j = e % HD;
-            ks[kk][j] = kk < tl ? ld<T>(kc, (size_t)(t0 + kk) * d + head * HD + j) : 0.f;
+        float kv[LPT];
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int e = tid + i * ATT_THREADS, kk = e / HD, j = e % HD;
+            kv[i] = ld<T>(kc, (size_t)(t0 + min(kk, tl - 1)) * d + head * HD + j);
+        }
+        float vv[LPT];
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int e = tid + i * ATT_THREADS;
+            const int kk = v_transposed ? e % ATT_TILE : e / HD, j = v_transposed ? e / ATT_TILE : e % HD;
+            vv[i] = v_transposed ? ld<T>(vc, (size_t)(head * HD + j) * max_seq + t0 + min(kk, tl - 1))
+                                 : ld<T>(vc, (size_t)(t0 + min(kk, tl - 1)) * d + head * HD + j);
+        }
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int e = tid + i * ATT_THREADS, kk = e / HD, j = e % HD;
+            ks[kk][j] = kk < tl ? kv[i] : 0.f;
         }
         __syncthreads();
-        for (int e = tid; e < ROWS * ATT_TILE; e += ATT_THREADS) {
+        for (int e = tid; e < rows * ATT_TILE; e += ATT_THREADS) {
             int r = e / ATT_TILE, kk = e % ATT_TILE;
             float s = -INFINITY;
-            if (r < rows && kk < tl && t0 + kk <= n + r) {     // causal inside the window
+            if (kk < tl && t0 + kk <= n + r) {     // causal inside the window
                 s = 0.f;
 #pragma unroll 8
                 for (int j = 0; j < HD; ++j) s = fmaf(qs[r][j], ks[kk][j], s);
@@ -73,38 +92,42 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(const float *
             sc[r][kk] = s;
         }
         __syncthreads();
-        // online softmax bookkeeping: one thread per row
-        if (tid < ROWS) {
-            const int r = tid;
-            float mx = m_run[r];
-            for (int kk = 0; kk < ATT_TILE; ++kk) mx = fmaxf(mx, sc[r][kk]);
-            float so = (mx == -INFINITY) ? 1.f : expf(m_run[r] - mx);
-            float sum = 0.f;
-            for (int kk = 0; kk < ATT_TILE; ++kk) {
-                float p = (sc[r][kk] == -INFINITY) ? 0.f : expf(sc[r][kk] - mx);
-                sc[r][kk] = p;
-                sum += p;
+        // online softmax bookkeeping: eight threads per row, eight keys each
+        {
+            static_assert(ROWS * 8 == ATT_THREADS && ATT_TILE == 64, "");
+            const int r = tid >> 3, k8 = (tid & 7) * 8;
+            if (r < rows) {
+                float mx = m_run[r];
+                const float m_old = mx;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) mx = fmaxf(mx, sc[r][k8 + k]);
+#pragma unroll
+                for (int o = 1; o < 8; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sc[r][k8 + k] = (sc[r][k8 + k] == -INFINITY) ? 0.f : expf(sc[r][k8 + k] - mx);
+                if ((tid & 7) == 0) { scale_old[r] = (mx == -INFINITY) ? 1.f : expf(m_old - mx); m_run[r] = mx; }
             }
-            l_run[r] = l_run[r] * so + sum;
-            m_run[r] = mx;
-            scale_old[r] = so;
         }
         // V tile into ks
-        for (int e = tid; e < ATT_TILE * HD; e += ATT_THREADS) {
-            int kk, j;
-            if (v_transposed) { j = e / ATT_TILE; kk = e % ATT_TILE; } else { kk = e / HD; j = e % HD; }
-            float v = 0.f;
-            if (kk < tl)
-                v = v_transposed ? ld<T>(vc, (size_t)(head * HD + j) * max_seq + t0 + kk)
-                                 : ld<T>(vc, (size_t)(t0 + kk) * d + head * HD + j);
-            ks[kk][j] = v;
+#pragma unroll
+        for (int i = 0; i < LPT; ++i) {
+            const int e = tid + i * ATT_THREADS;
+            const int kk = v_transposed ? e % ATT_TILE : e / HD, j = v_transposed ? e / ATT_TILE : e % HD;
+            ks[kk][j] = kk < tl ? vv[i] : 0.f;
         }
         __syncthreads();
+        if (tid < rows) {
+            float sum = 0.f;
+#pragma unroll 16
+            for (int kk = 0; kk < ATT_TILE; ++kk) sum += sc[tid][kk];
+            l_run[tid] = l_run[tid] * scale_old[tid] + sum;
+        }
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
             const int r = pv_g + i * RG;
-            if (r < ROWS) {
+            if (r < rows) {
                 float a = acc[i] * scale_old[r];
+#pragma unroll 16
                 for (int kk = 0; kk < ATT_TILE; ++kk) a = fmaf(sc[r][kk], ks[kk][pv_j], a);
                 acc[i] = a;
             }
