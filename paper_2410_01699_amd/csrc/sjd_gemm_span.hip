@@ -47,6 +47,7 @@ __device__ __forceinline__ bf16x8 lo_by_perm(bf16x8 hi, u32x2_t lo8)
 
 #define SPAN_AGENT 16             // cache policy sc1: stores go through to memory, loads come from there, whichever XCD asks
 #define SPAN_OOB 0x40000000u      // a byte offset behind every buffer: the load returns zeros and costs no memory access
+#define SPAN_K_MAX (1 << 21)      // (a buffer is at most 384 K bytes)
 
 template <int MT, int TN, int G, int WK, int EPI, bool NORM, int KSM>
 __global__ __launch_bounds__(64 * WK) void gemm_span_kernel(const bf16_t *__restrict__ Wp, const void *__restrict__ Xv,
@@ -299,7 +300,7 @@ static int launch_sliced_t(const SjdLinear *lin, const void *act, const SjdGemmE
 int sjd_launch_gemm_sliced(const SjdLinear *lin, const void *act, int32_t rows, const SjdGemmEpi &ep, int g, int ks,
                            const SjdPartials &part, hipStream_t s)
 {
-    if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn != 1 || lin->N % 16 || lin->K % 32 || ks < 1) return SJD_EINVAL;
+    if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn != 1 || lin->N % 16 || lin->K % 32 || lin->K > SPAN_K_MAX || ks < 1) return SJD_EINVAL;
     if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
     int mt = (rows + 15) / 16;
     if (mt > 4) mt = (mt + 1) & ~1;
@@ -341,7 +342,7 @@ bool sjd_sliced_plan(const SjdLinear *lin, int32_t rows, int *g, int *ks)
     const int tiles = lin->N / 16, KT = lin->K / 32;
     const bool longk = lin->K >= 2 * lin->N, few = rows <= SJD_ROWS_SKINNY;
     *g = *ks = 1;
-    if (!lin->resid || lin->tn != 1) return false;
+    if (!lin->resid || lin->tn != 1 || lin->K > SPAN_K_MAX) return false;
     if (tiles >= 256) {
         if (longk ? !few : few || rows > 64) return false;
         *g = *ks = longk ? 8 : 4;
@@ -368,6 +369,7 @@ size_t sjd_sliced_elems(const SjdLinear *lin)
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 {
     const int groups = lin->N / 16 / lin->tn, tiles = span_groups(lin) * lin->tn;
+    if (lin->K > SPAN_K_MAX) return false;
     if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4;
     const int64_t act = (int64_t)((rows + 15) / 16 * 16) * lin->K * 3;
     return tiles >= 3 || act <= 600 * 1024;
@@ -376,7 +378,7 @@ bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
                          const SjdGemmEpi &ep, hipStream_t s)
 {
-    if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn < 1 || lin->tn > 3 || lin->N % (16 * lin->tn) || lin->K % 32) return SJD_EINVAL;
+    if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn < 1 || lin->tn > 3 || lin->N % (16 * lin->tn) || lin->K % 32 || lin->K > SPAN_K_MAX) return SJD_EINVAL;
     if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
     const int tn = lin->tn, g = span_groups(lin);
     int mt = (rows + 15) / 16;
