@@ -419,24 +419,42 @@ static int forward_rows_f32(sjd_model *m, sjd_kv *kv, int32_t rows, int32_t rows
                             hipStream_t s)
 {
     const SjdState *st = kv->state;
-    const SjdLinear *prev = nullptr;   // GEMM whose output still has to be added to x
     const double kv_bytes_layer = kv->prof ? 2.0 * kv->prof_kv_tokens * m->cfg.d_model * 4
                                            : 2.0 * ((stream ? kv->n_upper_u : kv->n_upper) + rows) * m->cfg.d_model * 4;
+    // Projections normalise their own input where a workgroup's LDS holds it; x then moves between two buffers, the other of
+    // which holds the normalised rows of wider models.
+    float *x = kv->x, *other = (float *)kv->h;
+    SjdGemmF32 plain, e;
+    memset(&plain, 0, sizeof(plain));
+    plain.kind = SJD_EPI_STORE; plain.out = kv->part;
+    auto normed = [&](const SjdLinear &lin, const void *gain, const float *add) {
+        if (sjd_f32_norm_fits(&lin, rows)) {
+            e.gain = (const float *)gain; e.add = add; e.x_out = other; e.eps = m->cfg.rms_eps;
+            PROF(kv, SJD_PROF_GEMM, lin_bytes(m, lin), sjd_launch_gemm_f32(&lin, x, rows, e, st, s));
+            std::swap(x, other);
+        } else {
+            PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_rmsnorm(m, x, add, add ? 1 : 0, 0, gain, rows, other, st, s));
+            PROF(kv, SJD_PROF_GEMM, lin_bytes(m, lin), sjd_launch_gemm_f32(&lin, other, rows, e, st, s));
+        }
+        return (int)SJD_OK;
+    };
+    const float *add = nullptr;        // output of the projection before, still to be added to x
     for (int l = 0; l < m->cfg.n_layers; ++l) {
         const SjdLayer &L = m->layers[l];
-        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_rmsnorm(m, kv->x, prev ? kv->part : nullptr, prev ? 1 : 0, 0, L.g1, rows, kv->h, st, s));
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.qkv), sjd_launch_gemm(0, &L.qkv, kv->h, rows, kv->part, st, s));
-        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_rope_kv(m, kv, l, stream, kv->part, 1, 0, rows, rows_valid, s));
+        e = plain; e.kind = SJD_EPI_QKV; e.out = kv->qact; e.cosT = m->rope_cos; e.sinT = m->rope_sin; e.hd = m->hd;
+        e.rows_valid = rows_valid; e.stream = stream;
+        e.kc = (float *)(stream ? kv->k_u : kv->k) + (size_t)l * kv->k_layer_stride;
+        e.vc = (float *)(stream ? kv->v_u : kv->v) + (size_t)l * kv->v_layer_stride;
+        SJD_TRY(normed(L.qkv, L.g1, add));
         PROF(kv, SJD_PROF_ATTENTION, kv_bytes_layer, sjd_launch_attention_f32(m, kv, l, rows, stream, s));
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm(0, &L.o, kv->att_out, rows, kv->part, st, s));
-        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_rmsnorm(m, kv->x, kv->part, 1, 0, L.g2, rows, kv->h, st, s));
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.gu), sjd_launch_gemm(0, &L.gu, kv->h, rows, kv->part, st, s));
-        PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_silu_mul(m, kv->part, 1, 0, rows, kv->ffn, st, s));
-        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.down), sjd_launch_gemm(0, &L.down, kv->ffn, rows, kv->part, st, s));
-        prev = &L.down;
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm_f32(&L.o, (const float *)kv->att_out, rows, plain, st, s));
+        e = plain; e.kind = SJD_EPI_SILU; e.out = (float *)kv->ffn;
+        SJD_TRY(normed(L.gu, L.g2, kv->part));
+        PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.down), sjd_launch_gemm_f32(&L.down, (const float *)kv->ffn, rows, plain, st, s));
+        add = kv->part;
     }
-    PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_rmsnorm(m, kv->x, kv->part, 1, 0, m->gf, rows, kv->h, st, s));
-    PROF(kv, SJD_PROF_GEMM, lin_bytes(m, m->lm), sjd_launch_gemm(0, &m->lm, kv->h, rows, logits, st, s));
+    e = plain; e.out = logits;
+    SJD_TRY(normed(m->lm, m->gf, add));
     return SJD_OK;
 }
 
@@ -1422,7 +1440,10 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
                                      SjdPartials{(float *)g.part, part_elems, (uint32_t *)g.tickets}, s));
     } else {
         HIP_TRY(hipMemcpyAsync(g.Ap, A, (size_t)M * K * es, hipMemcpyDeviceToDevice, s));
-        SJD_TRY(sjd_launch_gemm(0, &lin, g.Ap, M, g.out, nullptr, s));
+        SjdGemmF32 ep;
+        memset(&ep, 0, sizeof(ep));
+        ep.kind = SJD_EPI_STORE; ep.out = g.out;
+        SJD_TRY(sjd_launch_gemm_f32(&lin, (const float *)g.Ap, M, ep, nullptr, s));
     }
     HIP_TRY(hipMemcpyAsync(C, g.out, (size_t)M * N * 4, hipMemcpyDeviceToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));

@@ -249,6 +249,19 @@ struct SjdGemmEpi {
     int32_t d, hd, hd_shift, nblk, rows_valid, max_seq;           // hd = 1 << hd_shift (32, 64 or 128); rows_valid: rows per stream whose K/V are stored
 };
 
+// what the fp32 GEMM does with its final values, and (gain set) the normalisation in front of it
+#define SJD_F32_NORM_MAX 4096     // rows x features a workgroup normalises by itself (16 KB of LDS)
+struct SjdGemmF32 {
+    int32_t kind;                                 // SJD_EPI_STORE, _SILU or _QKV
+    float *out;                                   // STORE: [rows][N]; SILU: [rows][N / 2]; QKV: the rotated queries [rows][d]
+    float *kc, *vc;                               // QKV: this layer's caches [position][d]
+    const float *cosT, *sinT;
+    int32_t hd, rows_valid, stream;
+    const float *gain, *add;                      // the input is x (+ add if set), normalised with this gain
+    float *x_out;                                 // receives x + add
+    float eps;
+};
+
 struct SjdLayer {
     const void *g1, *g2;
     SjdLinear qkv, o, gu, down;  // qkv: rows [Wq; Wk; Wv]; gu: rows [Wg; Wu]
@@ -349,14 +362,9 @@ int sjd_launch_embed(const sjd_model *m, const int32_t *const *ids, int32_t id_r
                      int32_t rows, const SjdStreams &sm, float *x, void *x24, float *ssq, int32_t *const *err, bool lo16, hipStream_t s);
 int sjd_launch_rmsnorm(const sjd_model *m, float *x, const float *part, int32_t n_part, size_t part_stride,
                        const void *gain, int32_t rows, void *h, const SjdState *st, hipStream_t s);
-int sjd_launch_rope_kv(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t stream, const float *part, int32_t n_part,
-                       size_t part_stride, int32_t rows, int32_t rows_valid, hipStream_t s);
-int sjd_launch_silu_mul(const sjd_model *m, const float *part, int32_t n_part, size_t part_stride, int32_t rows,
-                        void *ffn, const SjdState *st, hipStream_t s);
-int sjd_launch_reduce_rows(const float *part, int32_t n_part, size_t part_stride, int32_t rows, int32_t cols,
-                           float *out, const SjdState *st, hipStream_t s);
-int sjd_launch_gemm(int32_t dtype, const SjdLinear *lin, const void *act, int32_t rows, float *part,
-                    const SjdState *st, hipStream_t s);
+bool sjd_f32_by8(const SjdLinear *lin, int32_t rows);
+bool sjd_f32_norm_fits(const SjdLinear *lin, int32_t rows);
+int sjd_launch_gemm_f32(const SjdLinear *lin, const float *act, int32_t rows, const SjdGemmF32 &ep, const SjdState *st, hipStream_t s);
 // scratch of the projections that cut K across workgroups: fp32 sums, and one zeroed counter per column group, which a launch
 // leaves zeroed
 #define SJD_TICKETS 1024

@@ -1,7 +1,7 @@
 // Element-wise pieces of the window forward (paper Sec. 4.1 Step 2; the decoder itself is the
-// Llama-style stack the workloads name): embedding gather for every model, and for the fp32 models
-// RMSNorm fused with the residual add, RoPE + KV-cache write and SiLU(gate)*up (bf16 models do all of
-// these inside their projection kernel).  All of them are bandwidth-trivial (rows <= 32).
+// Llama-style stack the workloads name): embedding gather for every model, and RMSNorm fused with the
+// residual add for fp32 models too wide to do it inside their projections (the rest of it is done there; in bf16
+// models everything is).  All of them are bandwidth-trivial (rows <= 32).
 #include "sjd_internal.h"
 
 template <typename T> struct Act;
@@ -83,76 +83,6 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float *x, const float *par
     for (int j = threadIdx.x; j < d; j += 256) Act<T>::store(h, (size_t)r * d + j, xr[j] * inv * Act<T>::load(gain, j));
 }
 
-// qkv[r][0:3d] = sum_p part[p][r][:];  rotate q and k (pairs j, j+hd/2) at position n+r;
-// q -> qact[r][d];  k -> K cache row n+r;  v -> V cache (bf16: transposed [head][hd][pos]).
-template <typename T>
-__global__ __launch_bounds__(256) void rope_kv_kernel(const float *part, int n_part, size_t part_stride, int d, int hd,
-                                                      int max_seq, const float *cosT, const float *sinT, float *qact,
-                                                      T *kc, T *vc, int v_transposed, int rows_valid,
-                                                      int stream, const SjdState *st)
-{
-    if (st->done) return;
-    const int r = blockIdx.x;
-    const int pos = state_n(st, stream) + r;
-    const int half = hd / 2;
-    const size_t row = (size_t)r * 3 * d;
-    for (int e = threadIdx.x; e < d / 2; e += 256) {
-        const int head = e / half, j = e % half;
-        const int c0 = head * hd + j, c1 = c0 + half;
-        float q0 = 0, q1 = 0, k0 = 0, k1 = 0, v0 = 0, v1 = 0;
-        for (int p = 0; p < n_part; ++p) {
-            const float *src = part + (size_t)p * part_stride + row;
-            q0 += src[c0]; q1 += src[c1];
-            k0 += src[d + c0]; k1 += src[d + c1];
-            v0 += src[2 * d + c0]; v1 += src[2 * d + c1];
-        }
-        const float c = cosT[(size_t)pos * half + j], s = sinT[(size_t)pos * half + j];
-        qact[(size_t)r * d + c0] = q0 * c - q1 * s;
-        qact[(size_t)r * d + c1] = q1 * c + q0 * s;
-        if (r < rows_valid) {
-            Act<T>::store(kc, (size_t)pos * d + c0, k0 * c - k1 * s);
-            Act<T>::store(kc, (size_t)pos * d + c1, k1 * c + k0 * s);
-            if (v_transposed) {
-                Act<T>::store(vc, (size_t)c0 * max_seq + pos, v0);
-                Act<T>::store(vc, (size_t)c1 * max_seq + pos, v1);
-            } else {
-                Act<T>::store(vc, (size_t)pos * d + c0, v0);
-                Act<T>::store(vc, (size_t)pos * d + c1, v1);
-            }
-        }
-    }
-}
-
-// ffn[r][f] = SiLU(g) * u with g = sum_p part[p][r][f], u = sum_p part[p][r][F + f]
-template <typename T>
-__global__ __launch_bounds__(256) void silu_mul_kernel(const float *part, int n_part, size_t part_stride, int F, T *ffn,
-                                                       const SjdState *st)
-{
-    if (st->done) return;
-    const int r = blockIdx.y;
-    const int f = blockIdx.x * 256 + threadIdx.x;
-    if (f >= F) return;
-    float g = 0, u = 0;
-    for (int p = 0; p < n_part; ++p) {
-        const float *src = part + (size_t)p * part_stride + (size_t)r * 2 * F;
-        g += src[f]; u += src[F + f];
-    }
-    Act<T>::store(ffn, (size_t)r * F + f, g / (1.0f + expf(-g)) * u);
-}
-
-// out[r][c] = sum_p part[p][r][c]
-__global__ __launch_bounds__(256) void reduce_rows_kernel(const float *part, int n_part, size_t part_stride, int cols,
-                                                          float *out, const SjdState *st)
-{
-    if (st && st->done) return;
-    const int r = blockIdx.y;
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= cols) return;
-    float v = 0;
-    for (int p = 0; p < n_part; ++p) v += part[(size_t)p * part_stride + (size_t)r * cols + c];
-    out[(size_t)r * cols + c] = v;
-}
-
 // ---------------------------------------------------------------------------------------------
 #define LAUNCH_CHECK() HIP_TRY(hipGetLastError())
 
@@ -187,39 +117,6 @@ int sjd_launch_rmsnorm(const sjd_model *m, float *x, const float *part, int32_t 
     if (m->cfg.dtype != 0) return SJD_EINVAL;   // bf16 models normalise inside the projection kernel
     SJD_LAUNCH(rmsnorm_kernel<float>, dim3(rows), dim3(256), 0, s, x, part, n_part, part_stride,
                        (const float *)gain, d, m->cfg.rms_eps, (float *)h, st);
-    LAUNCH_CHECK();
-    return SJD_OK;
-}
-
-int sjd_launch_rope_kv(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t stream, const float *part, int32_t n_part,
-                       size_t part_stride, int32_t rows, int32_t rows_valid, hipStream_t s)
-{
-    const int d = m->cfg.d_model, ms = m->cfg.max_seq;
-    if (m->cfg.dtype != 0) return SJD_EINVAL;   // bf16 models do this in the QKV GEMM epilogue
-    float *kc = (float *)(stream ? kv->k_u : kv->k), *vc = (float *)(stream ? kv->v_u : kv->v);
-    SJD_LAUNCH(rope_kv_kernel<float>, dim3(rows), dim3(256), 0, s, part, n_part, part_stride, d, m->hd, ms,
-                       m->rope_cos, m->rope_sin, kv->qact, kc + (size_t)layer * kv->k_layer_stride,
-                       vc + (size_t)layer * kv->v_layer_stride, 0, rows_valid, stream, kv->state);
-    LAUNCH_CHECK();
-    return SJD_OK;
-}
-
-int sjd_launch_silu_mul(const sjd_model *m, const float *part, int32_t n_part, size_t part_stride, int32_t rows,
-                        void *ffn, const SjdState *st, hipStream_t s)
-{
-    const int F = m->cfg.d_ffn;
-    if (m->cfg.dtype != 0) return SJD_EINVAL;   // bf16 models do this in the gate/up epilogue
-    dim3 grid((F + 255) / 256, rows);
-    SJD_LAUNCH(silu_mul_kernel<float>, grid, dim3(256), 0, s, part, n_part, part_stride, F, (float *)ffn, st);
-    LAUNCH_CHECK();
-    return SJD_OK;
-}
-
-int sjd_launch_reduce_rows(const float *part, int32_t n_part, size_t part_stride, int32_t rows, int32_t cols,
-                           float *out, const SjdState *st, hipStream_t s)
-{
-    dim3 grid((cols + 255) / 256, rows);
-    SJD_LAUNCH(reduce_rows_kernel, grid, dim3(256), 0, s, part, n_part, part_stride, cols, out, st);
     LAUNCH_CHECK();
     return SJD_OK;
 }
