@@ -8,7 +8,7 @@
 
 #define SJD_ROWS_MAX SJD_MAX_ROWS       // rows (window slots of all streams, or a prefill chunk) one forward pass handles
 #define SJD_MTILES (SJD_ROWS_MAX / 16)  // 16-row tiles of an activation matrix
-#define SJD_ROWS_SKINNY 32              // up to here the skinny projection kernel runs, above it the wide one
+#define SJD_ROWS_SKINNY 32              // up to here the skinny projection kernel runs, above it the wide one, where the span kernel does not
 #define SJD_ROWS_F32 32                 // fp32 models (launch-bound toys): rows per forward, largest window
 
 typedef unsigned short bf16_t;  // raw bf16 bit pattern
