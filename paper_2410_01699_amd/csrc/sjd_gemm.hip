@@ -19,8 +19,10 @@ __device__ __forceinline__ float sum_rows(float (&a)[MR], int lane)
         const bool up = (lane & o) != 0;
 #pragma unroll
         for (int i = 0; i < half; ++i) {
-            const float send = up ? a[i] : a[i + half], keep = up ? a[i + half] : a[i];
-            a[i] = keep + __shfl_xor(send, o);
+            // (values, chosen between as values: a choice of elements makes the compiler index the array by selects, 4500 of
+            // them in the store variant of 32 rows)
+            const float lo = a[i], hi = a[i + half];
+            a[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, o);
         }
     }
 #pragma unroll
@@ -117,17 +119,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
     for (int t = 0; t < NF; ++t)
 #pragma unroll
         for (int m = 0; m < MR; ++m) acc[t][m] = 0.f;
+    constexpr int RC = MR < 16 ? MR : 16;
     for (int k4 = lane; k4 < K / 4; k4 += 64) {
         if (k4 >= 64) {
 #pragma unroll
             for (int t = 0; t < NF; ++t) w[t] = w4[t][k4];
         }
+        // The rows' values are requested together, 16 at a time (64 registers): left alone the store variants waited for each
+        // row's load by itself.  Two layers of d = 1024, 4096 hidden, 8192 logits at 8, 16 and 32 rows 182, 300 and 605 us, now
+        // 123, 166 and 260 (128, 512 and 1024: 64, 73 and 88, now 58, 66 and 81); all 32 at once 269, 8 at a time 273.
 #pragma unroll
-        for (int m = 0; m < MR; ++m) {
-            const float4 a = reinterpret_cast<const float4 *>((NORM ? hs : A) + (size_t)min(m, rows - 1) * K)[k4];
+        for (int m0 = 0; m0 < MR; m0 += RC) {
+            float4 a[RC];
 #pragma unroll
-            for (int t = 0; t < NF; ++t)
-                acc[t][m] = fmaf(w[t].x, a.x, fmaf(w[t].y, a.y, fmaf(w[t].z, a.z, fmaf(w[t].w, a.w, acc[t][m]))));
+            for (int m = 0; m < RC; ++m) a[m] = reinterpret_cast<const float4 *>((NORM ? hs : A) + (size_t)min(m0 + m, rows - 1) * K)[k4];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < RC; ++m)
+#pragma unroll
+                for (int t = 0; t < NF; ++t)
+                    acc[t][m0 + m] = fmaf(w[t].x, a[m].x, fmaf(w[t].y, a[m].y, fmaf(w[t].z, a[m].z, fmaf(w[t].w, a[m].w, acc[t][m0 + m]))));
         }
     }
     float v[NF];
