@@ -288,6 +288,15 @@ int sjd_dist(const float *logits, int32_t rows, int32_t V_s, const sjd_sampler *
 int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_t M, int32_t N, int32_t K, float *C,
                   void *stream);
 
+/* Which kernel a projection of a bf16 model (M rows, N x K weights) runs on, without running it (no GPU needed).  resid: its
+ * output is added to the residual stream (O, down).  *kernel: SJD_GEMM_*; *tn: 16-feature tiles per packed weight group; *g: weight
+ * groups per workgroup (span, sliced) or per wave (wide), else 1; *ks: K-slices.                 */
+#define SJD_GEMM_SKINNY 0    /* up to 32 rows: a group per workgroup, its waves split K                        */
+#define SJD_GEMM_SPAN 1      /* a workgroup owns its groups for the whole reduction, at any row count           */
+#define SJD_GEMM_SLICED 2    /* the same with K cut into slices whose sums meet in one launch                    */
+#define SJD_GEMM_WIDE 3      /* waves split N, K cut into slices, a second kernel adds them                      */
+int sjd_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t resid, int32_t *kernel, int32_t *tn, int32_t *g, int32_t *ks);
+
 /* Tuning aid: average microseconds per launch of the bf16 projection kernel (plain-store epilogue) at
  * shape M x N x K over `iters` back-to-back launches on zero-filled operands (activations in the
  * 3-byte form the model's projections read).  `tn` = output tiles

@@ -25,7 +25,7 @@ EXPORTS = ["sjd_init_model", "sjd_free_model", "sjd_kv_create", "sjd_kv_free", "
            "sjd_verify", "sjd_verify_probs", "sjd_dist", "sjd_gemm_test", "sjd_strerror", "sjd_decode_begin",
            "sjd_decode_steps", "sjd_decode_status", "sjd_decode_result", "sjd_kv_use_graph", "sjd_profile_steps", "sjd_gemm_bench",
            "sjd_prefill_uncond", "sjd_generate_cfg", "sjd_decode_steps_batch", "sjd_forward_logits_batch",
-           "sjd_generate_batch", "sjd_profile_steps_batch", "sjd_verify_static"]
+           "sjd_generate_batch", "sjd_profile_steps_batch", "sjd_verify_static", "sjd_gemm_plan"]
 
 PROF_KINDS = ("gemm", "attention", "elementwise", "verify")
 
@@ -98,6 +98,7 @@ _SIG = {
                                    _vp, _vp]),
     "sjd_dist": (C.c_int, [_vp, _i32, _i32, _P(sjd_sampler), _vp, _vp, _vp]),
     "sjd_gemm_test": (C.c_int, [_i32, _vp, _vp, _i32, _i32, _i32, _vp, _vp]),
+    "sjd_gemm_plan": (C.c_int, [_i32, _i32, _i32, _i32, _P(_i32), _P(_i32), _P(_i32), _P(_i32)]),
     "sjd_strerror": (C.c_char_p, [C.c_int]),
     "sjd_decode_begin": (C.c_int, [_vp, _vp, _vp, _i32, _i32, _P(sjd_sampler), _P(sjd_init), _u64, _vp]),
     "sjd_decode_steps": (C.c_int, [_vp, _vp, _i32, _vp]),
@@ -286,6 +287,16 @@ def sjd_dist(logits, rows, V_s, smp, forced, q, stream=None):
 
 def sjd_gemm_test(dtype, A, W, M, N, K, Cout, stream=None):
     _check(_lib.sjd_gemm_test(dtype, _dev(A), _dev(W), M, N, K, _dev(Cout), _stream(stream)))
+
+
+GEMM_KERNELS = ("skinny", "span", "sliced", "wide")
+
+
+def sjd_gemm_plan(M, N, K, resid=False):
+    """(kernel name, tiles per weight group, groups per workgroup or wave, K-slices) of a bf16 projection; needs no GPU"""
+    r = [_i32(0) for _ in range(4)]
+    _check(_lib.sjd_gemm_plan(M, N, K, int(resid), *[C.byref(x) for x in r]))
+    return (GEMM_KERNELS[r[0].value], *[x.value for x in r[1:]])
 
 
 def sjd_decode_begin(m, kv, q_first, N, L, smp, init, seed, stream=None):

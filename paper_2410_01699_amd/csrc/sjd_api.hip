@@ -1450,6 +1450,19 @@ extern "C" int sjd_gemm_test(int32_t dtype, const void *A, const void *W, int32_
     return SJD_OK;
 }
 
+extern "C" int sjd_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t resid, int32_t *kernel, int32_t *tn, int32_t *g, int32_t *ks)
+{
+    if (M < 1 || M > SJD_ROWS_MAX || N < 16 || K < 32 || N % 16 || K % 32 || !kernel || !tn || !g || !ks) return SJD_EINVAL;
+    SjdLinear lin;
+    memset(&lin, 0, sizeof(lin));
+    lin.N = N; lin.K = K;
+    sjd_choose_tiles(&lin);
+    lin.resid = resid ? 1 : 0;
+    *kernel = sjd_gemm_route(&lin, M, g, ks);
+    *tn = lin.tn;
+    return SJD_OK;
+}
+
 // The floor for a kernel that has to read `bytes` of weights: a plain streaming read of them (workgroup b takes
 // a contiguous share, its four waves a quarter each, four 16-byte loads per lane in flight), nothing else.
 typedef __attribute__((ext_vector_type(4))) float stream_f32x4;

@@ -372,11 +372,21 @@ static int launch_epi(const SjdLinear *lin, const void *act, const float *ssq_in
     }
 }
 
+int sjd_gemm_route(const SjdLinear *lin, int32_t rows, int *g, int *ks)
+{
+    if (sjd_sliced_plan(lin, rows, g, ks)) return SJD_GEMM_SLICED;
+    *g = *ks = 1;
+    if (sjd_span_takes(lin, rows)) { *g = sjd_span_groups(lin); return SJD_GEMM_SPAN; }
+    if (rows <= SJD_ROWS_SKINNY && !(lin->wide_from > 0 && rows >= lin->wide_from)) return SJD_GEMM_SKINNY;
+    int kps;
+    sjd_wide_plan(lin, ((rows + 15) / 16 + 1) & ~1, SIZE_MAX, g, ks, &kps);
+    return SJD_GEMM_WIDE;
+}
+
 int sjd_gemm_form(const SjdLinear *lin, int32_t rows)
 {
     int g, ks;
-    if (sjd_sliced_plan(lin, rows, &g, &ks) || sjd_span_takes(lin, rows)) return SJD_ACT_P3;
-    return rows > SJD_ROWS_SKINNY || (lin->wide_from > 0 && rows >= lin->wide_from) ? SJD_ACT_P4 : SJD_ACT_P3;
+    return sjd_gemm_route(lin, rows, &g, &ks) == SJD_GEMM_WIDE ? SJD_ACT_P4 : SJD_ACT_P3;
 }
 
 int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const float *ssq_in, float eps, int32_t rows,

@@ -314,7 +314,7 @@ int sjd_launch_gemm_sliced(const SjdLinear *lin, const void *act, int32_t rows, 
 
 // packed weight groups per workgroup: one workgroup per CU where six tiles a workgroup allow it (eight waves hold the sums of
 // 24 fragments and two k-steps of operands in 256 registers each, four waves 48 in 512)
-static int span_groups(const SjdLinear *lin)
+int sjd_span_groups(const SjdLinear *lin)
 {
     const int groups = lin->N / 16 / lin->tn;
     return std::max(1, std::min((groups + 255) / 256, 6 / lin->tn > 3 ? 3 : 6 / lin->tn));
@@ -352,7 +352,7 @@ bool sjd_sliced_plan(const SjdLinear *lin, int32_t rows, int *g, int *ks)
         *ks = 512 / tiles >= 8 ? 8 : 512 / tiles >= 4 ? 4 : 2;
     }
     while (*ks > 1 && KT / *ks < 8) *ks /= 2;             // (a k-step for every wave)
-    return *ks > 1;
+    return *ks > 1 && (tiles + *g - 1) / *g <= SJD_TICKETS;
 }
 
 // floats of slices' sums of such a projection at most, over all row counts
@@ -368,7 +368,7 @@ size_t sjd_sliced_elems(const SjdLinear *lin)
 
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 {
-    const int groups = lin->N / 16 / lin->tn, tiles = span_groups(lin) * lin->tn;
+    const int groups = lin->N / 16 / lin->tn, tiles = sjd_span_groups(lin) * lin->tn;
     if (lin->K > SPAN_K_MAX) return false;
     if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4;
     const int64_t act = (int64_t)((rows + 15) / 16 * 16) * lin->K * 3;
@@ -380,7 +380,7 @@ int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq
 {
     if (rows < 1 || rows > SJD_ROWS_MAX || lin->tn < 1 || lin->tn > 3 || lin->N % (16 * lin->tn) || lin->K % 32 || lin->K > SPAN_K_MAX) return SJD_EINVAL;
     if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
-    const int tn = lin->tn, g = span_groups(lin);
+    const int tn = lin->tn, g = sjd_span_groups(lin);
     int mt = (rows + 15) / 16;
     if (mt > 4) mt = (mt + 1) & ~1;                       // variants for 16, 32, 48, 64, 96 and 128 rows
 #define CASE(MT, TN, G) if (mt == MT && tn == TN && g == G) return launch_span_t<MT, TN, G>(lin, act, ssq_in, eps, ep, s)

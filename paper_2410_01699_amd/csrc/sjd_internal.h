@@ -391,6 +391,10 @@ int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq
 int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,
                          const SjdGemmEpi &ep, hipStream_t s);
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows);
+int sjd_span_groups(const SjdLinear *lin);
+// the kernel (SJD_GEMM_*) that a projection over `rows` rows runs on, its weight groups per workgroup (span, sliced) or wave (wide)
+// and its K-slices
+int sjd_gemm_route(const SjdLinear *lin, int32_t rows, int *g, int *ks);
 // the form in which a projection over `rows` rows wants its activations: what their producer writes
 int sjd_gemm_form(const SjdLinear *lin, int32_t rows);
 void sjd_wide_plan(const SjdLinear *lin, int mt, size_t part_elems, int *g_out, int *ks_out, int *kps_out);

@@ -55,6 +55,11 @@ def test_wide_ragged(B, M, N, K):        # noqa: F811
     forward.test_gemm_against_fp64(B, 2, M, N, K)
 
 
+# 4097 one-tile groups: more columns of workgroups than a sliced launch has counters for
+def test_more_columns_than_counters(B):        # noqa: F811
+    forward.test_gemm_against_fp64(B, 2, 40, 65552, 512)
+
+
 # Whoever arrives last adds the slices, always in the same order: a forward has the same bits every time.
 @pytest.mark.parametrize("L", [16, 64])
 def test_sliced_sums_have_one_order(B, L):        # noqa: F811
