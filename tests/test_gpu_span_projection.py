@@ -38,6 +38,13 @@ def test_spans_up_to_32_rows(B, M, N, K):        # noqa: F811
     forward.test_gemm_against_fp64(B, 2, M, N, K)
 
 
+# walks of 8 to 15 k-steps a wave, which start at different k-steps: 8 each, 10 each, 12 with 11 in the last, 15 with 11
+@pytest.mark.parametrize("M", [16, 32, 64, 128])
+@pytest.mark.parametrize("K", [2048, 2560, 3040, 3712])
+def test_short_walks_start_apart(B, M, K):        # noqa: F811
+    forward.test_gemm_against_fp64(B, 2, M, 16384, K)
+
+
 # K cut into slices (tn = 1 everywhere): 8 tiles x 8 slices up to 32 rows, also with three ragged tiles and a short last
 # slice; 4 x 4 at 33 .. 64; 2 tiles x 4 slices (96 tiles), 2 x 4 with one tile in the last column, 2 x 8 (16 tiles, 8 and 9
 # k-steps a slice), 2 x 2 (16 k-steps)
