@@ -367,13 +367,20 @@ size_t sjd_sliced_elems(const SjdLinear *lin)
     return most;
 }
 
+// Only with one workgroup per CU: more of them are a second round that is mostly empty, each reading all activations again.
+// One projection alone on cold weights, skinny or wide kernel and span:
+//  - 32768 x 4096, 342 workgroups: 16 rows 42.9 and 50.3 us, 64 rows 58.9 and 67.2, 128 rows 73.9 and 102.7
+//  - 27648 x 5120 in one-tile groups, 576: 64 rows 69.3 and 81.7, 128 rows 93.9 and 124.8; forwards of two such layers (d = 5120,
+//    8192 logits) of 64, 96 and 128 rows had become 449, 570 and 701 us, 437, 531 and 626 before
+// Two-tile groups at 17 to 32 rows are the exception: 32768 x 4096 53.3 and 55.2, x 7168 100.8 and 94.7, 57344 x 8192 187.7 and 172.3.
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 {
-    const int groups = lin->N / 16 / lin->tn, tiles = sjd_span_groups(lin) * lin->tn;
+    const int groups = lin->N / 16 / lin->tn, g = sjd_span_groups(lin), tiles = g * lin->tn;
+    const bool one_round = (groups + g - 1) / g <= 256;
     if (lin->K > SPAN_K_MAX) return false;
-    if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4;
+    if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4 && (one_round || (rows > 16 && lin->tn == 2));
     const int64_t act = (int64_t)((rows + 15) / 16 * 16) * lin->K * 3;
-    return tiles >= 3 || act <= 600 * 1024;
+    return one_round && (tiles >= 3 || act <= 600 * 1024);
 }
 
 int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,

@@ -24,3 +24,20 @@ def test_what_a_plan_promises(M):
                     assert ks == 1 and (kernel == "span" or M <= 32)
                 else:
                     assert M > 32
+
+
+# A second round of workgroups that own their features is mostly empty: such projections run on the skinny and the wide kernel (two-tile
+# groups at 17 to 32 rows excepted).  (27648, 5120), (18432, 6144), (32768, 6144), (28672, 4096), (44032, 8192): gate/up and QKV of wide
+# decoders, 342 to 918 workgroups.
+@pytest.mark.parametrize("M", [1, 16, 17, 32, 33, 48, 64, 65, 96, 128])
+def test_spans_are_one_round(M):
+    wide = [(27648, 5120), (18432, 6144), (32768, 6144), (28672, 4096), (44032, 8192), (36864, 7168)]
+    for N, K in wide:
+        kernel, tn, g, ks = B.sjd_gemm_plan(M, N, K)
+        assert kernel == ("wide" if M > 32 else "span" if M > 16 and (N, K) == (32768, 6144) else "skinny")
+    for tiles in range(1, 5000, 7):
+        for K in (512, 4096, 8192):
+            kernel, tn, g, ks = B.sjd_gemm_plan(M, tiles * 16, K)
+            assert kernel != "span" or -(-tiles // tn // g) <= 256 or (16 < M <= 32 and tn == 2)
+    # what fills the chip in one round stays: 7B QKV and gate/up above 32 rows, gate/up at any row count
+    assert B.sjd_gemm_plan(M, 22016, 4096)[0] == "span" and (B.sjd_gemm_plan(M, 12288, 4096)[0] == "span") == (M > 32)
