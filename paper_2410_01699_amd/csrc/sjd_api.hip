@@ -409,6 +409,14 @@ static int window_max(const sjd_model *m, bool guided)
     return m->cfg.dtype == 1 ? w : std::min(w, SJD_ROWS_F32);
 }
 
+// upper bound of the cached positions that a window forward of all handles reads
+static double batch_tokens_upper(sjd_kv *const *kvs, int32_t B, int32_t L)
+{
+    double toks = 0;
+    for (int b = 0; b < B; ++b) toks += kvs[b]->n_upper + L + (kvs[0]->cfg_on ? kvs[b]->n_upper_u + L : 0);
+    return toks;
+}
+
 // ---- the window forward (Step 2) ------------------------------------------------------------
 // rows = rows computed, rows_valid = rows whose K/V are written.  Inputs already in kv->x.
 static double lin_bytes(const sjd_model *m, const SjdLinear &l) { return (double)l.N * l.K * elt_size(m->cfg.dtype); }
@@ -493,7 +501,7 @@ static SjdStreams handle_streams(const sjd_kv *kv, int32_t stream_mode, int32_t 
 // bf16: RMSNorm, residual adds, SiLU*up, RoPE and the cache write happen inside the projection kernel.
 // `rows` rows per stream of `sm` (inputs already in kv->x, stream i at row i << sm.shift; the logits
 // land in the same rows of `logits`).  The activation buffers are kv's; the caches are the streams'.
-// kv_tokens_upper: upper bound of the cached positions all streams together read (profiling only).
+// kv_tokens_upper: upper bound of the cached positions all streams together read (a captured iteration: at its generation's end).
 static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int32_t rows, int32_t rows_valid,
                              double kv_tokens_upper, float *logits, hipStream_t s)
 {
@@ -504,7 +512,8 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
     auto form = [&](const SjdLinear &lin) { return sjd_gemm_form(&lin, grows); };
     auto lo16 = [&](const SjdLinear &lin) { return form(lin) == SJD_ACT_P4; };
     // upper bound of the K/V bytes one layer's attention reads (hi + lo planes)
-    const double kv_bytes_layer = 2.0 * kv_tokens_upper * d * 4;
+    const double kv_bytes_layer = 2.0 * (kv->prof ? kv->prof_kv_tokens : kv_tokens_upper) * d * 4;
+    const bool kv_streams = sjd_kv_streams(m, kv_tokens_upper);
     SjdGemmEpi e_qkv, e_res, e_silu, e_lm;
     memset(&e_qkv, 0, sizeof(e_qkv));
     e_qkv.sm = sm;
@@ -525,7 +534,7 @@ static int forward_rows_bf16(sjd_model *m, sjd_kv *kv, const SjdStreams &sm, int
         const SjdLinear &next = l + 1 < m->cfg.n_layers ? m->layers[l + 1].qkv : m->lm;
         e_qkv.layer_off = (size_t)l * kv->k_layer_stride;
         PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.qkv), sjd_launch_gemm_bf16(&L.qkv, x, form(L.qkv), ssq, eps, grows, e_qkv, part, s));
-        PROF(kv, SJD_PROF_ATTENTION, kv_bytes_layer, sjd_launch_attention(m, kv, l, rows, sm, lo16(L.o), s));
+        PROF(kv, SJD_PROF_ATTENTION, kv_bytes_layer, sjd_launch_attention(m, kv, l, rows, sm, lo16(L.o), kv_streams, s));
         e_res.gain_next = (const bf16_t *)L.g2; e_res.lo16 = lo16(L.gu);
         PROF(kv, SJD_PROF_GEMM, lin_bytes(m, L.o), sjd_launch_gemm_bf16(&L.o, att, form(L.o), nullptr, 0.f, grows, e_res, part, s));
         e_silu.lo16 = lo16(L.down);
@@ -551,9 +560,7 @@ static int forward_window(sjd_model *m, sjd_kv *kv, const int32_t *ids, int32_t 
         int32_t *errv[SJD_MAX_STREAMS] = {&kv->state->err, &kv->state->err};
         const bool lo16 = sjd_gemm_form(&m->layers[0].qkv, ((sm.count - 1) << sm.shift) + rows) == SJD_ACT_P4;
         PROF(kv, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, idv, id_rows, emb_rows, rows, sm, kv->x, kv->x24, kv->ssq, errv, lo16, s));
-        // (only the profiler uses the count: it has read the true lengths before the iteration)
-        const double toks = kv->prof ? kv->prof_kv_tokens
-                                     : (stream_mode == 1 ? 0 : kv->n_upper + rows) + (stream_mode == 0 ? 0 : kv->n_upper_u + rows);
+        const double toks = (stream_mode == 1 ? 0 : kv->n_upper + rows) + (stream_mode == 0 ? 0 : kv->n_upper_u + rows);
         return forward_rows_bf16(m, kv, sm, rows, rows_valid, toks, logits, s);
     }
     // fp32 models are launch-bound toys: two streams are two forwards
@@ -824,6 +831,9 @@ extern "C" int sjd_decode_begin(sjd_model *m, sjd_kv *kv, const float *q_first, 
     kv->last_stream = s;
     kv->n_upper += N;                    // the loop never fixes more than N tokens
     kv->n_upper_u += N;
+    const bool kv_streams = sjd_kv_streams(m, batch_tokens_upper(&kv, 1, L));
+    if (kv->graph_kv_streams != kv_streams) drop_graph(kv);       // (the captured step's attention reads its cache the other way)
+    kv->graph_kv_streams = kv_streams;
     return SJD_OK;
 }
 
@@ -948,10 +958,7 @@ static int forward_batch(sjd_model *m, sjd_kv *const *kvs, int32_t B, const int3
     }
     const bool lo16 = sjd_gemm_form(&m->layers[0].qkv, ((sm.count - 1) << sm.shift) + L) == SJD_ACT_P4;
     PROF(kv0, SJD_PROF_ELEMENTWISE, 0, sjd_launch_embed(m, ids_s, L, nullptr, L, sm, kv0->x, kv0->x24, kv0->ssq, errv, lo16, s));
-    double toks = 0;
-    for (int b = 0; b < B; ++b) toks += kvs[b]->n_upper + L + (kv0->cfg_on ? kvs[b]->n_upper_u + L : 0);
-    if (kv0->prof) toks = kv0->prof_kv_tokens;
-    return forward_rows_bf16(m, kv0, sm, L, L, toks, kv0->logits, s);
+    return forward_rows_bf16(m, kv0, sm, L, L, batch_tokens_upper(kvs, B, L), kv0->logits, s);
 }
 
 static int decode_one_batch(sjd_model *m, sjd_kv *const *kvs, int32_t B, hipStream_t s)
@@ -999,6 +1006,7 @@ extern "C" int sjd_decode_steps_batch(sjd_model *m, sjd_kv *const *kvs, int32_t 
         if (kv0->cfg_on) { key.cache_u[b] = kvs[b]->k_u; key.cfg_scale[b] = kvs[b]->cfg_scale; }
     }
     key.cfg_on = kv0->cfg_on;
+    key.kv_streams = sjd_kv_streams(m, batch_tokens_upper(kvs, B, kv0->dec_L));
     if (kv0->bgraph_exec && memcmp(&key, &kv0->bkey, sizeof(key)) != 0) drop_batch_graph(kv0);
     if (!kv0->bgraph_exec) {
         // one iteration of all handles; what varies between iterations lives in device memory

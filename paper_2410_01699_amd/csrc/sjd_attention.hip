@@ -212,13 +212,17 @@ __device__ __forceinline__ void arrive_and_wait()
 //  - two waves per SIMD, at most 256 registers each (left alone the compiler took 316 for heads of 128 and 32 queries, one
 //    workgroup per CU): the scores of every query tile come first, so that the key tiles' registers are free before the
 //    probabilities are made (1240 positions x 2 contexts of 32 queries: 35.7 -> 27.1 us, 23.1 with what follows);
-//  - keys and values as non-temporal loads (each is read once a forward; a plain read of this chip runs at 6.4 TB/s with
-//    them and at 5.9 without): one context of 16 drafts at 3967 positions 3422 -> 3348 us, eight at 583 6400 -> 6330;
+//  - keys and values as non-temporal loads (NT: a plain read of this chip runs at 6.4 TB/s with them and at 5.9 without) where one
+//    query group reads them and the forward's caches are more than the last-level cache can keep (sjd_kv_streams).  Plain loads
+//    and non-temporal ones, us a forward: 7B, eight images of 16 drafts at 1239 positions (10 GB) 7204 and 6888, at 583
+//    6262 and 6192, one at 583 (0.6 GB) 2756 and 2736.  Smaller caches are still there when the next forward reads them, and when
+//    the QKV epilogue writes into their lines, unless they were read so: 775M, one image at 633 positions (0.19 GB) 773 and 789, eight
+//    at 200 1628 and 1649, 7B at 100 (0.1 GB) 2632 and 2648.  Two query groups, 775M window of 64 at 1100 positions 1190 and 1215;
 //  - loads in the order of their use (Q, K, V; the next block's K during the probabilities), as global accesses with
 //    nothing conditional between a load and its use, so that each wait is for its own loads only; and the arguments of the
 //    first loads in registers (16 queries at 600 positions: 8.3 -> 6.7 us; 7B forward of 16 drafts there 2998 -> 2942).
 // partial record of (head, split): O[MT*16][HD] unnormalised, then m[MT*16], then l[MT*16]
-template <int HD, int MT, int AW>
+template <int HD, int MT, int AW, bool NT>
 __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n0, const int32_t *done0, const bf16_t *kvc0,
                                                             const float *__restrict__ qact, int d, int nblk_cache,
                                                             int rows, int splits, int qgroups, int shift,
@@ -271,6 +275,7 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
     }
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 ka[2][KS][2], va[DT][2];
+    auto load_once = [](const SJD_GLOBAL bf16x8 *p) -> bf16x8 { if constexpr (NT) return __builtin_nontemporal_load(p); else return *p; };
     auto load_k = [&](int blk) {
         const SJD_GLOBAL bf16x8 *rec = reinterpret_cast<const SJD_GLOBAL bf16x8 *>(kvc + kv_block_off(head, blk, nblk_cache, HD)) + lane;
 #pragma unroll
@@ -278,14 +283,14 @@ __global__ __launch_bounds__(64 * AW, 2) void attn_split_kernel(const int32_t *n
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int pl = 0; pl < 2; ++pl) ka[h][ks][pl] = __builtin_nontemporal_load(rec + ((h * KS + ks) * 2 + pl) * 64);
+                for (int pl = 0; pl < 2; ++pl) ka[h][ks][pl] = load_once(rec + ((h * KS + ks) * 2 + pl) * 64);
     };
     auto load_v = [&](int blk) {
         const SJD_GLOBAL bf16x8 *rec = reinterpret_cast<const SJD_GLOBAL bf16x8 *>(kvc + kv_block_off(head, blk, nblk_cache, HD)) + lane;
 #pragma unroll
         for (int t = 0; t < DT; ++t)
 #pragma unroll
-            for (int pl = 0; pl < 2; ++pl) va[t][pl] = __builtin_nontemporal_load(rec + (2 * KS * 2 + t * 2 + pl) * 64);
+            for (int pl = 0; pl < 2; ++pl) va[t][pl] = load_once(rec + (2 * KS * 2 + t * 2 + pl) * 64);
     };
     // Q as B operand, shared by the waves: entry [mt][ks][plane][lane] holds
     // Q[query c (+16 mt)][32 ks + 8 g .. +8], scaled by 1/sqrt(HD), as hi and lo bf16 planes
@@ -562,7 +567,7 @@ static bool eight_waves(int hd, int heads, int pairs, int att_splits)
 
 template <int HD, int MT>
 static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, const SjdStreams &sm, bool lo16,
-                         hipStream_t s)
+                         bool kv_streams, hipStream_t s)
 {
     const int d = m->cfg.d_model, H = m->cfg.n_heads;
     const size_t off = (size_t)layer * kv->k_layer_stride;
@@ -571,10 +576,16 @@ static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t 
     const int splits = eight ? 256 / (H * pairs) : key_splits(HD, H, pairs, kv->att_splits);
     if (pairs * splits > 2 * std::max(kv->att_splits, SJD_MAX_STREAMS / 2)) return SJD_EINVAL;    // (what att_part holds)
     const int grows = std::min(rows, MT * 16);
-#define GO(W) SJD_LAUNCH((attn_split_kernel<HD, MT, W>), dim3(H, splits, pairs), dim3(64 * W), 0, s, sm.first.n, sm.first.done, \
+#define GO(W, NT) SJD_LAUNCH((attn_split_kernel<HD, MT, W, NT>), dim3(H, splits, pairs), dim3(64 * W), 0, s, sm.first.n, sm.first.done, \
                        sm.first.kvc + off, kv->qact, d, kv->nblk, rows, splits, qgroups, sm.shift, kv->att_part, sm.table, off, \
                        kv->att_out, lo16 ? 1 : 0)
-    if constexpr (HD == 128) { if (eight) GO(8); else GO(4); } else GO(4);
+    const bool nt = kv_streams && qgroups == 1;
+    if constexpr (HD == 128) {
+        if (eight && nt) GO(8, true);
+        else if (eight) GO(8, false);
+    }
+    if (!eight && nt) GO(4, true);
+    else if (!eight) GO(4, false);
 #undef GO
     HIP_TRY(hipGetLastError());
     if (splits == 1) return SJD_OK;               // (written in place)
@@ -586,22 +597,22 @@ static int launch_mfma_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t 
 
 template <int HD>
 static int launch_mfma(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, const SjdStreams &sm, bool lo16,
-                       hipStream_t s)
+                       bool kv_streams, hipStream_t s)
 {
     if (sm.count < 1 || sm.count > SJD_MAX_STREAMS || rows > (1 << sm.shift) || (sm.count << sm.shift) > SJD_ROWS_MAX)
         return SJD_EINVAL;
-    if (rows <= 16) return launch_mfma_t<HD, 1>(m, kv, layer, rows, sm, lo16, s);
-    return launch_mfma_t<HD, 2>(m, kv, layer, rows, sm, lo16, s);     // 32 queries per (stream, query group)
+    if (rows <= 16) return launch_mfma_t<HD, 1>(m, kv, layer, rows, sm, lo16, kv_streams, s);
+    return launch_mfma_t<HD, 2>(m, kv, layer, rows, sm, lo16, kv_streams, s);     // 32 queries per (stream, query group)
 }
 
 int sjd_launch_attention(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, const SjdStreams &sm, bool lo16,
-                         hipStream_t s)
+                         bool kv_streams, hipStream_t s)
 {
     const int hd = m->hd;
     if (m->cfg.dtype != 1) return SJD_EINVAL;
-    if (hd == 32) return launch_mfma<32>(m, kv, layer, rows, sm, lo16, s);
-    if (hd == 64) return launch_mfma<64>(m, kv, layer, rows, sm, lo16, s);
-    if (hd == 128) return launch_mfma<128>(m, kv, layer, rows, sm, lo16, s);
+    if (hd == 32) return launch_mfma<32>(m, kv, layer, rows, sm, lo16, kv_streams, s);
+    if (hd == 64) return launch_mfma<64>(m, kv, layer, rows, sm, lo16, kv_streams, s);
+    if (hd == 128) return launch_mfma<128>(m, kv, layer, rows, sm, lo16, kv_streams, s);
     return SJD_EINVAL;
 }
 

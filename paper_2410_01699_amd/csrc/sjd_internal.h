@@ -338,7 +338,7 @@ struct sjd_kv {
         const void *kv[SJD_MAX_STREAMS], *state[SJD_MAX_STREAMS], *cache[SJD_MAX_STREAMS], *ring[SJD_MAX_STREAMS];
         const void *cache_u[SJD_MAX_STREAMS];      // guided batches: the handles' second caches ...
         float cfg_scale[SJD_MAX_STREAMS];          // ... and their guidance weights
-        int32_t cfg_on;
+        int32_t cfg_on, kv_streams;
         uint64_t seed[SJD_MAX_STREAMS];
     } bkey;
     SjdStreamEntry *cfg_tab;                   // device [2]: the two contexts of this handle under guidance
@@ -348,6 +348,7 @@ struct sjd_kv {
     int32_t ring_rows;
     int32_t graph_cfg_on;   // stream mode and guidance weight the captured iteration was recorded with
     float graph_cfg_scale;
+    int32_t graph_kv_streams;   // how its attention reads the cache (sjd_kv_streams)
     void *prof;           // SjdProfiler* while sjd_profile_steps runs, else NULL
     double prof_kv_tokens;   // while profiling: cached positions (all streams) the next iteration's attention reads
 };
@@ -407,7 +408,14 @@ int sjd_bf16_rows_to_act24(const bf16_t *src, int32_t rows, int32_t K, void *dst
 int sjd_launch_attention_f32(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, int32_t stream, hipStream_t s);
 // bf16 models: `rows` query rows per stream of sm against that stream's cache
 int sjd_launch_attention(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, const SjdStreams &sm, bool lo16,
-                         hipStream_t s);
+                         bool kv_streams, hipStream_t s);
+// Whether caches of `positions` positions together (bf16 models) stream past the last-level cache: more than 512 MB, twice its size.
+// In between non-temporal loads are 0.7 % of a forward ahead (775M, two images at 633 positions, 0.37 GB) to 1.3 % behind (eight at
+// 200, 0.41 GB).
+inline bool sjd_kv_streams(const sjd_model *m, double positions)
+{
+    return positions * m->cfg.n_layers * m->cfg.d_model * 8 > 512 << 20;
+}
 int32_t sjd_attention_splits(const sjd_model *m);
 size_t sjd_attention_part_elems(const sjd_model *m);
 // sampling / verification

@@ -106,3 +106,33 @@ def test_heads_of_eight_waves(B, wide_heads, images, L):        # noqa: F811
         rel = float(np.linalg.norm(got[b] - ref) / np.linalg.norm(ref))
         forward._say(f"image over {n} positions, {images} x {L}: {err:.3e}, 2-norm {rel:.3e}")
         assert err < forward.TOL_BF16 and rel < REL, (n, err, rel)
+
+
+# Keys and values are read with non-temporal loads where the caches of a forward may hold more than 512 MB, else with plain ones:
+# the same bits either way.  A handle counts with the positions it may have reached, so a generation that has begun and may go on for
+# 17000 tokens reads the same few positions the other way.  Heads of 32, 64 and 128, the latter with eight waves and (24 heads) with
+# four, one query tile and two.
+@pytest.mark.parametrize("layers,d,heads", [(4, 1024, 32), (2, 2048, 32), (1, 4096, 32), (2, 3072, 24)])
+def test_both_ways_to_read_the_cache(B, layers, d, heads):        # noqa: F811
+    n_more = 17000
+    shape = synth.ModelShape(layers, d, heads, 512, 512, 256, 512, n_more + 600, synth.DTYPE_BF16)
+    assert 8 * d * layers * n_more > 512 << 20 > 8 * d * layers * 600
+    m = B.sjd_init_model(B.config_from_shape(shape), synth.make_weights(shape, seed=9, std=0.036, threads=16))
+    kv = B.sjd_kv_create(m)
+    try:
+        q = torch.empty(shape.v_s, dtype=torch.float32, device="cuda")
+        smp, init = B.sjd_sampler(8, 1.0), B.sjd_init(0, 0, -1)
+        B.sjd_prefill(m, kv, synth.random_tokens(403, 0, 256, seed=1), None, smp, init, q)
+        outs = []
+        for _ in range(2):
+            for L in (1, 16, 29):
+                toks = forward._dev(synth.random_tokens(L, 256, 512, seed=L))
+                outs.append(torch.empty((L, shape.v_s), dtype=torch.float32, device="cuda"))
+                B.sjd_forward_logits(m, kv, toks, L, outs[-1])
+            B.sjd_decode_begin(m, kv, q, n_more, 16, smp, init, 7)
+        torch.cuda.synchronize()
+        for a, b in zip(outs[:3], outs[3:]):
+            assert torch.isfinite(a).all() and a.abs().max() > 0 and torch.equal(a, b)
+    finally:
+        B.sjd_kv_free(kv)
+        B.sjd_free_model(m)
