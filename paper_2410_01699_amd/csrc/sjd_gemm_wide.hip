@@ -171,10 +171,12 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wide_kernel(const bf16_t *__r
 // planes held x * gain and ssq_in the per-16-feature sums of squares of x), and runs the epilogue.
 // Workgroup (x, mt): M-tile mt, the `ft` n tiles of column group x, one per wave; lane l of a wave holds features
 // 16 ntile + 4 (l / 16) .. + 4 of token 16 mt + l % 16, exactly as the MFMA left them.  What it costs is latency: a
-// launch, one round of loads, the stores.  So everything (up to sixteen slices, the epilogue's operands, the sums of
-// squares) is requested before anything is used, and the workgroups are cut like those of the first kernel: with both
+// launch, one round of loads, the stores.  So everything (up to QS slices, the epilogue's operands, the sums of
+// squares) is requested before anything is used: sixteen slices where there are more than four (775M down projection 4.65 -> 4.1 us
+// a launch), else four, so that 64 registers are enough and two workgroups of 1024 threads share a CU (sixteen for all: 94;
+// gate/up of 44032 features at 96 rows 11.6 -> 16.9 us, of 32768 at 128 11.4 -> 16.0); and the workgroups are cut like those of the first kernel: with both
 // grids a multiple of eight column groups wide, a group's slices and its epilogue meet in one XCD's L2.
-template <int EPI, int PRO>
+template <int EPI, int PRO, int QS>
 __global__ __launch_bounds__(1024) void gemm_wide_epilogue_kernel(const f32x4 *__restrict__ part, int KS, int MT, int NT,
                                                                  const float *__restrict__ ssq_in, float eps, int N, int K,
                                                                  SjdGemmEpi ep)
@@ -186,11 +188,11 @@ __global__ __launch_bounds__(1024) void gemm_wide_epilogue_kernel(const f32x4 *_
     const int nt = blockIdx.x * ft + wave, ntile = min(nt, NT - 1);            // (past the end: the last tile, not written)
     const f32x4 *p = part + ((size_t)mt * NT + ntile) * 64 + lane;
     const size_t step = (size_t)MT * NT * 64;                     // from one slice to the next
-    f32x4 q[16];
+    f32x4 q[QS];
 #pragma unroll
     for (int i = 0; i < 4; ++i) q[i] = p[(size_t)min(i, KS - 1) * step];
 #pragma unroll
-    for (int i = 4; i < 16; i += 4) {
+    for (int i = 4; i < QS; i += 4) {
         if (i >= KS) break;
 #pragma unroll
         for (int j = i; j < i + 4; ++j) q[j] = p[(size_t)min(j, KS - 1) * step];
@@ -217,8 +219,8 @@ __global__ __launch_bounds__(1024) void gemm_wide_epilogue_kernel(const f32x4 *_
     }
     f32x4 v = q[0];
 #pragma unroll
-    for (int i = 1; i < 16; ++i) if (i < KS) v += q[i];
-    for (int y = 16; y < KS; ++y) v += p[(size_t)y * step];
+    for (int i = 1; i < QS; ++i) if (i < KS) v += q[i];
+    for (int y = QS; y < KS; ++y) v += p[(size_t)y * step];
     if (PRO == SJD_PRO_NORM) v *= rs[c];
     if (nt < NT) apply_epilogue<EPI>(ep, N, f_m, f_n0, v, pre);
 }
@@ -364,7 +366,8 @@ int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq
     const int NT = lin->N / 16;
     dim3 grid(wide_cols(NT / lin->tn, g, ks), mt);
     const dim3 block(64 * WIDE_WAVES * g * lin->tn);      // 256 .. 1024
-#define GO(EPI, PRO) SJD_LAUNCH((gemm_wide_epilogue_kernel<EPI, PRO>), grid, block, 0, s, p4, ks, mt, NT, ssq_in, eps, lin->N, lin->K, ep)
+#define LAUNCH(EPI, PRO, QS) SJD_LAUNCH((gemm_wide_epilogue_kernel<EPI, PRO, QS>), grid, block, 0, s, p4, ks, mt, NT, ssq_in, eps, lin->N, lin->K, ep)
+#define GO(EPI, PRO) do { if (ks <= 4) LAUNCH(EPI, PRO, 4); else LAUNCH(EPI, PRO, 16); } while (0)
     if (ssq_in) {
         switch (ep.kind) {
             case SJD_EPI_STORE: GO(SJD_EPI_STORE, SJD_PRO_NORM); break;
@@ -380,6 +383,7 @@ int sjd_launch_gemm_wide(const SjdLinear *lin, const void *act, const float *ssq
         }
     }
 #undef GO
+#undef LAUNCH
     HIP_TRY(hipGetLastError());
     return SJD_OK;
 }
