@@ -321,13 +321,6 @@ int sjd_span_groups(const SjdLinear *lin)
     return std::max(1, std::min((groups + 255) / 256, 6 / lin->tn > 3 ? 3 : 6 / lin->tn));
 }
 
-// Which projections come here.  Up to 32 rows: those that leave the skinny kernel with two or more workgroups per CU (7B
-// gate/up above; the LM head of the 775M model 10.5 -> 10.7 us alone at 16 rows, 13.4 -> 12.0 at 32).  More rows: the
-// alternative is the wide kernel, which reads the activations once for eight tiles but pays a second kernel (4-5 us) and the
-// slices' traffic.  With three tiles or more per workgroup reading all activations is the smaller price (7B QKV inside a forward: 64 rows
-// 28.6 us against 23.3 + 8.2, 128 rows 43.8 against 30.4 + 12.3; forwards of 64 and 128 rows 1.2 % and 1.1 % faster);
-// with fewer, as long as they are few bytes: all 775M projections but down (K = 1536; 295 KB at 64 rows, 590 at 128) gain
-// 14 % of a forward of 64 rows and 5 % of one of 121; 7B O at 64 rows (786 KB) makes its forward 1.7 % slower.
 // Which projections are cut into K-slices here, and how: G groups of one tile a workgroup, KS slices.  O and down only (their
 // output is added to the residual stream), where a workgroup with all of K reads more activations than weights or CUs stay
 // without a workgroup:
@@ -337,7 +330,11 @@ int sjd_span_groups(const SjdLinear *lin)
 //  - 256 tiles and more, other K (7B O), 33 to 64 rows: 4 x 4; forward of 2 x 32 rows 4251 -> 4202 us, prompt of 64 3880 -> 3808.
 //    At 128 rows it loses (5962 -> 5994), up to 32 the skinny kernel alone needs 8.2 and 10.8 us, sliced 9.9 and 11.1.
 //  - fewer tiles (775M, 96 of them for 256 CUs): 2 x 4.  down at 16, 64, 121 rows 8.1 -> 7.0, 7.4 + 4.1 -> 8.3, 10.1 + 5.1 -> 12.4 us, O at
-//    64 rows 8.7 -> 8.3; O up to 32 rows is faster whole (4.3 us alone against 5.0).
+//    64 rows 8.7 -> 8.3; O up to 32 rows is faster whole (4.3 us alone against 5.0), and so is what has fewer than 72 k-steps:
+//    512 x 2048 at 16 rows alone skinny 4.8, sliced 5.5, x 2304 5.4 and 5.3.
+//  - more than 128 of them leave two slices, 2 x 2, and a long share of the activations for each: alone, wide kernel and sliced, 3072 x
+//    3072 10.7 and 10.7 us at 64 rows, 12.2 and 13.8 at 96; long K, 3072 x 8192 20.8 and 18.7 at 48 rows, 20.8 and 21.4 at 64, 25.3 and 32.6
+//    at 128, 3584 x 18944 44.9 and 40.0, 45.0 and 46.8, 46.4 and 72.4.  So up to 64 rows, with a long K up to 48.
 bool sjd_sliced_plan(const SjdLinear *lin, int32_t rows, int *g, int *ks)
 {
     const int tiles = lin->N / 16, KT = lin->K / 32;
@@ -348,7 +345,7 @@ bool sjd_sliced_plan(const SjdLinear *lin, int32_t rows, int *g, int *ks)
         if (longk ? !few : few || rows > 64) return false;
         *g = *ks = longk ? 8 : 4;
     } else {
-        if (few && !longk) return false;
+        if (few ? !longk || KT < 72 : tiles > 128 && rows > (longk ? 48 : 64)) return false;
         *g = 2;
         *ks = 512 / tiles >= 8 ? 8 : 512 / tiles >= 4 ? 4 : 2;
     }
@@ -367,6 +364,14 @@ size_t sjd_sliced_elems(const SjdLinear *lin)
     return most;
 }
 
+// Which projections come here.  Up to 32 rows: those that leave the skinny kernel with two or more workgroups per CU (7B
+// gate/up above; the LM head of the 775M model 10.5 -> 10.7 us alone at 16 rows, 13.4 -> 12.0 at 32).  More rows: the
+// alternative is the wide kernel, which reads the activations once for eight tiles but pays a second kernel (4-5 us) and the
+// slices' traffic.  With three tiles or more per workgroup reading all activations is the smaller price (7B QKV inside a forward: 64 rows
+// 28.6 us against 23.3 + 8.2, 128 rows 43.8 against 30.4 + 12.3; forwards of 64 and 128 rows 1.2 % and 1.1 % faster);
+// with fewer, as long as they are few bytes: all 775M projections but down (K = 1536; 295 KB at 64 rows, 590 at 128) gain
+// 14 % of a forward of 64 rows and 5 % of one of 121; 7B O at 64 rows (786 KB) makes its forward 1.7 % slower.
+//
 // Only with one workgroup per CU: more of them are a second round that is mostly empty, each reading all activations again.
 // One projection alone on cold weights, skinny or wide kernel and span:
 //  - 32768 x 4096, 342 workgroups: 16 rows 42.9 and 50.3 us, 64 rows 58.9 and 67.2, 128 rows 73.9 and 102.7

@@ -41,3 +41,14 @@ def test_spans_are_one_round(M):
             assert kernel != "span" or -(-tiles // tn // g) <= 256 or (16 < M <= 32 and tn == 2)
     # what fills the chip in one round stays: 7B QKV and gate/up above 32 rows, gate/up at any row count
     assert B.sjd_gemm_plan(M, 22016, 4096)[0] == "span" and (B.sjd_gemm_plan(M, 12288, 4096)[0] == "span") == (M > 32)
+
+
+# Few tiles (O and down of narrow decoders) are cut in K where that is faster: not the short reductions up to 32 rows, and in two slices
+# (129 to 255 tiles) only while a slice's share of the activations is small.
+@pytest.mark.parametrize("N,K,rows", [(512, 2048, (33, 128)), (1024, 2048, (33, 128)), (512, 2304, (1, 128)), (1536, 4096, (1, 128)),
+                                      (2048, 8192, (1, 128)), (1536, 1536, (33, 128)), (3072, 3072, (33, 64)), (2560, 6912, (1, 48)),
+                                      (3072, 8192, (1, 48)), (3584, 18944, (1, 48)), (4096, 4096, (33, 64)), (4096, 11008, (1, 32))])
+def test_where_slices_pay(N, K, rows):
+    for M in range(1, 129):
+        kernel = B.sjd_gemm_plan(M, N, K, resid=True)[0]
+        assert (kernel == "sliced") == (rows[0] <= M <= rows[1]), (M, kernel)
