@@ -378,6 +378,7 @@ size_t sjd_sliced_elems(const SjdLinear *lin)
 //  - 27648 x 5120 in one-tile groups, 576: 64 rows 69.3 and 81.7, 128 rows 93.9 and 124.8; forwards of two such layers (d = 5120,
 //    8192 logits) of 64, 96 and 128 rows had become 449, 570 and 701 us, 437, 531 and 626 before
 // Two-tile groups at 17 to 32 rows are the exception: 32768 x 4096 53.3 and 55.2, x 7168 100.8 and 94.7, 57344 x 8192 187.7 and 172.3.
+// Nor above 64 rows of 8192 features and more (2.4 MB of activations for every workgroup at 96 rows): 24576 x 8192 alone 72.3 and 73.1 us at 64 rows, 79.7 and 86.5 at 96, 95.5 and 101.1 at 128; 16384 x 8192 at 128 73.6 and 86.6; 21504 x 7168 97.1 and 86.4.
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 {
     const int groups = lin->N / 16 / lin->tn, g = sjd_span_groups(lin), tiles = g * lin->tn;
@@ -385,7 +386,7 @@ bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
     if (lin->K > SPAN_K_MAX) return false;
     if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4 && (one_round || (rows > 16 && lin->tn == 2));
     const int64_t act = (int64_t)((rows + 15) / 16 * 16) * lin->K * 3;
-    return one_round && (tiles >= 3 || act <= 600 * 1024);
+    return one_round && (rows <= 64 || lin->K < 8192) && (tiles >= 3 || act <= 600 * 1024);
 }
 
 int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq_in, float eps, int32_t rows,

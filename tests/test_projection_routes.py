@@ -39,6 +39,8 @@ def test_spans_are_one_round(M):
         for K in (512, 4096, 8192):
             kernel, tn, g, ks = B.sjd_gemm_plan(M, tiles * 16, K)
             assert kernel != "span" or -(-tiles // tn // g) <= 256 or (16 < M <= 32 and tn == 2)
+    # long reductions above 64 rows
+    assert B.sjd_gemm_plan(M, 24576, 8192)[0] == ("wide" if M > 64 else "span")
     # what fills the chip in one round stays: 7B QKV and gate/up above 32 rows, gate/up at any row count
     assert B.sjd_gemm_plan(M, 22016, 4096)[0] == "span" and (B.sjd_gemm_plan(M, 12288, 4096)[0] == "span") == (M > 32)
 
