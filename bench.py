@@ -166,7 +166,7 @@ def main():
         rows_out = []
         for M_ in [int(x) for x in args.gemm_sweep.split(",")]:
             for name, (N_, K_, tn_) in shapes.items():
-                res = {"model's choice": B.sjd_gemm_bench(M_, N_, K_, tn_, 0, 0, -40)}
+                res = {"model's choice": B.sjd_gemm_bench(M_, N_, K_, tn_, -1 if name.endswith(("_o", "_down")) else 0, 0, -40)}
                 # plain reads of the same weight bytes: by as many workgroups as the skinny kernel launches, each a
                 # contiguous share (the kernel's own pattern), and the fastest plain read found (many workgroups
                 # sweeping the bytes together)

@@ -304,8 +304,8 @@ int sjd_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t resid, int32_t *kerne
  * prefetch stage (2; 4 for wk = 4, M <= 16; 0 = the choice the model makes).
  * wk >= 200: the span kernel with K cut into wk - 200 slices whose sums meet in one launch, u one-tile groups per workgroup
  * (u = 2 with up to 8 slices, 8 with up to 8 slices and 32 rows, 4 with up to 4 at 33 .. 64 rows; tn = 1).
- * wk = u = 0 runs the kernel that the model would: for large N (two or more workgroups per CU otherwise), and above
- * 32 rows for most shapes, the span kernel (one workgroup per CU owns its features for the whole reduction).
+ * wk = u = 0 runs the kernel that the model would for QKV, gate/up and the LM head (sjd_gemm_plan with resid = 0), wk = -1 and
+ * u = 0 the one for O and down (resid = 1), provided that tn is the packing the plan gives.
  * More than 32 rows otherwise run the wide kernel (waves split N and share the activations through LDS, K split
  * across workgroups, a second kernel adds the slices): then wk = K-slices and u = weight groups per wave
  * (0 = automatic); wk >= 100 asks for the wide kernel at any row count, with wk - 100 K-slices.  M above

@@ -1550,13 +1550,18 @@ extern "C" int sjd_gemm_bench(int32_t M, int32_t N, int32_t K, int32_t tn, int32
     const int chunks = (M + SJD_ROWS_MAX - 1) / SJD_ROWS_MAX, rows = chunks > 1 ? SJD_ROWS_MAX : M;
     // wk >= 100 asks for the wide kernel at any row count, with wk - 100 K-slices (0 = automatic) and u
     // weight groups per wave (0 = automatic)
+    const bool model = chunks == 1 && u == 0 && (wk == 0 || wk == -1);        // the model's choice (-1: for O and down)
+    SjdLinear lin;
+    memset(&lin, 0, sizeof(lin));
+    lin.N = N; lin.K = K; lin.tn = tn; lin.resid = wk == -1;
+    if (model) wk = 0;
     const bool sliced = wk >= 200;
     if (sliced) wk -= 200;
     const bool force_wide = !sliced && wk >= 100;
     if (force_wide) wk -= 100;
     const bool wide = rows > SJD_ROWS_SKINNY || force_wide;
     // skinny kernel: u + 10 reads the activations in their 4-byte form (2-byte lo plane) instead of 3 bytes
-    int form = wide && !sliced ? SJD_ACT_P4 : SJD_ACT_P3;
+    int form = model ? sjd_gemm_form(&lin, rows) : wide && !sliced ? SJD_ACT_P4 : SJD_ACT_P3;
     if (!wide && !sliced && u >= 10) { u -= 10; form = SJD_ACT_P4; }
     if (!wide && !sliced && (u != 0 && u != 2 && u != 4)) return SJD_EINVAL;       // (0: the model's choice)
     const size_t wbytes = (size_t)N * K * 2;
@@ -1565,15 +1570,13 @@ extern "C" int sjd_gemm_bench(int32_t M, int32_t N, int32_t K, int32_t tn, int32
     SJD_TRY(dev_alloc(&g.Ap, (size_t)SJD_ROWS_MAX * K * 4 + 2048));
     SJD_TRY(dev_alloc(&g.Wp, wbytes * copies));
     SJD_TRY(dev_alloc((void **)&g.out, (size_t)SJD_ROWS_MAX * N * 4));
-    const size_t part_elems = wide || sliced ? (size_t)8 * SJD_ROWS_MAX * (N + 128) : 0;      // (room for up to 8 K-slices)
+    // (room for up to 8 K-slices; the model's choice: for as many as the model has)
+    const size_t part_elems = model ? std::max(sjd_wide_part_elems(&lin), sjd_sliced_elems(&lin)) : wide || sliced ? (size_t)8 * SJD_ROWS_MAX * (N + 128) : 0;
     if (part_elems) SJD_TRY(dev_alloc(&g.part, part_elems * 4));
     SJD_TRY(dev_alloc(&g.tickets, SJD_TICKETS * 4));
-    SjdLinear lin;
-    memset(&lin, 0, sizeof(lin));
-    lin.N = N; lin.K = K; lin.tn = tn; lin.w = g.Wp;
-    if (!force_wide && chunks == 1 && wk == 0 && u == 0 && sjd_span_takes(&lin, rows)) form = SJD_ACT_P3;       // the model's choice: the span kernel
-    else if (wide) { lin.wks = wk; lin.wg = u; lin.wide_from = 1; }      // wide kernel: K-slices and weight groups per wave (0 = automatic)
-    else { lin.wk = wk; lin.u = u; }
+    lin.w = g.Wp;
+    if (!model && wide) { lin.wks = wk; lin.wg = u; lin.wide_from = 1; }      // wide kernel: K-slices and weight groups per wave (0 = automatic)
+    else if (!model) { lin.wk = wk; lin.u = u; }
     SjdGemmEpi ep;
     memset(&ep, 0, sizeof(ep));
     ep.kind = SJD_EPI_STORE; ep.out = g.out; ep.rows_out = rows;

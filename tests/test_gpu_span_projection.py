@@ -101,3 +101,19 @@ def test_span_precision(B, M, N, K):        # noqa: F811
     rel = float((C.double() - ref).norm() / ref.norm())
     forward._say(f"{M} x {N} x {K}: {rel:.3e} from 64 bits")
     assert rel < 3.0e-7
+
+
+# The tuning aid's "model's choice" for O and down is the sliced kernel where the model runs it (7B down at 32 rows 21 us, skinny
+# kernel 30).  At more rows it has room for as many slices as a handle.
+def test_model_choice_of_the_tuning_aid(B):        # noqa: F811
+    def us(wk, u):
+        return min(B.sjd_gemm_bench(32, 4096, 11008, 1, wk, u, -20) for _ in range(3))
+
+    model, sliced, skinny = us(-1, 0), us(208, 8), us(0, 0)
+    forward._say(f"model's choice {model:.1f} us, sliced {sliced:.1f}, skinny {skinny:.1f}")
+    assert abs(model - sliced) < abs(model - skinny)
+    for M, N, K in ((64, 1536, 4096), (128, 4096, 11008), (128, 1536, 1536)):
+        assert B.sjd_gemm_bench(M, N, K, 1, -1, 0, -3) > 0
+    for wk, u in ((-1, 2), (-2, 0)):
+        with pytest.raises(B.SjdError):
+            B.sjd_gemm_bench(16, 4096, 4096, 1, wk, u, -3)
