@@ -61,13 +61,13 @@ class Gpu:
                                          # bf16 weights, fp32 activations handed over in 3 bytes per value
                                          (2, 16, 4096, 11008), (2, 32, 4096, 4096), (2, 7, 48, 96), (2, 32, 1536, 4096),
                                          (2, 21, 256, 320),
-                                         # 17..32 rows of a shape whose N alone fills the chip: the wide kernel's
-                                         # whole-K variant (three waves per workgroup, epilogue in the kernel), with
-                                         # a last workgroup of one and of two weight groups, and a reduction shorter
-                                         # than one pipeline stage
+                                         # 17..32 rows of a shape whose N alone fills the chip: the span kernel (a
+                                         # workgroup owns three or two weight groups for the whole reduction), also with
+                                         # a reduction shorter than one k-step per wave
                                          (2, 32, 22016, 4096), (2, 21, 22016, 4096), (2, 25, 16384, 96),
-                                         # more than 32 rows: the wide kernel (waves split N, K-slices added by a
-                                         # second kernel), at the four 7B shapes + LM head, at 775M shapes, and at
+                                         # more than 32 rows: the span kernel, whole (7B QKV and gate/up, 775M QKV) and in
+                                         # K-slices (O at 64 rows, 775M down), the wide kernel (waves split N, K-slices
+                                         # added by a second kernel: 7B O at 128 rows, down and the LM head), and
                                          # ragged sizes (rows not a multiple of 16, fewer weight groups than waves)
                                          (1, 64, 12288, 4096), (2, 128, 12288, 4096), (1, 128, 4096, 4096),
                                          (2, 64, 4096, 4096), (2, 128, 4096, 11008), (1, 64, 4096, 11008),
@@ -220,7 +220,7 @@ def test_forward_775m_bf16(B):
     blob = synth.make_weights(w.shape, seed=0)
     ids, emb = synth.make_prompt(w)
     toks = synth.random_tokens(64, 0, w.shape.v_s, seed=4)
-    # (the 32-row window sends the LM head, 16384 outputs, through the wide kernel's whole-K variant)
+    # (the LM head, 16384 outputs, runs on the span kernel at any row count)
     worst = _check_forward(B, w.shape, blob, ids, [(toks[:16], 6), (toks[16:32], 16), (toks[32:64], 20)], TOL_BF16, embeds=emb)
     _say(f"775m bf16 worst {worst:.3e}")
 
@@ -366,7 +366,7 @@ def test_step_errors(B):
 def test_forward_and_step_7b_full_size(B, workload, window):
     """The 7B workloads at their real shape (32 layers, d=4096, 8192 sampled codes of 65536; window 16 on the
     32 x 32 grid, window 32 with a forced row-end token every 49 positions on the 48 x 48 grid, and a window
-    of 64, which runs on the wide projection kernel): every logit of one window against the fp64 oracle,
+    of 64, for the span, sliced and wide projection kernels): every logit of one window against the fp64 oracle,
     then one whole sjd_step whose verification must be bit-exact given the GPU's logits."""
     import dataclasses
     w = synth.WORKLOADS[workload]
@@ -562,7 +562,7 @@ def test_forward_bf16_long_cache_window32(B):
 
 
 def test_forward_bf16_windows_above_32_rows(B):
-    """windows of 33 .. 128 rows (the wide projection kernel; attention in query groups of 32) on a cache
+    """windows of 33 .. 128 rows (span projections, whole and in K-slices; attention in query groups of 32) on a cache
     that grows past several 32-position blocks, and a prompt pre-filled in chunks of 128 rows"""
     shape = synth.ModelShape(4, 256, 4, 512, 2048, 1024, 2048, 700, synth.DTYPE_BF16)
     blob = synth.make_weights(shape, seed=7)
