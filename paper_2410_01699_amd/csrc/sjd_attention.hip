@@ -22,8 +22,7 @@ template <> __device__ __forceinline__ void st_act<float>(float *p, int r, int c
 // part layout per (head, split): [rows][hd] unnormalised output, then m[rows], then l[rows]
 template <typename T, int HD>
 __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(const float *__restrict__ qact, const T *__restrict__ kc,
-                                                                   const T *__restrict__ vc, int d, int max_seq,
-                                                                   int rows, int v_transposed, int splits,
+                                                                   const T *__restrict__ vc, int d, int rows, int splits,
                                                                    float *__restrict__ part, int stream,
                                                                    const SjdState *st)
 {
@@ -70,10 +69,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(const float *
         float vv[LPT];
 #pragma unroll
         for (int i = 0; i < LPT; ++i) {
-            const int e = tid + i * ATT_THREADS;
-            const int kk = v_transposed ? e % ATT_TILE : e / HD, j = v_transposed ? e / ATT_TILE : e % HD;
-            vv[i] = v_transposed ? ld<T>(vc, (size_t)(head * HD + j) * max_seq + t0 + min(kk, tl - 1))
-                                 : ld<T>(vc, (size_t)(t0 + min(kk, tl - 1)) * d + head * HD + j);
+            const int e = tid + i * ATT_THREADS, kk = e / HD, j = e % HD;
+            vv[i] = ld<T>(vc, (size_t)(t0 + min(kk, tl - 1)) * d + head * HD + j);
         }
 #pragma unroll
         for (int i = 0; i < LPT; ++i) {
@@ -111,8 +108,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_partial_kernel(const float *
         // V tile into ks
 #pragma unroll
         for (int i = 0; i < LPT; ++i) {
-            const int e = tid + i * ATT_THREADS;
-            const int kk = v_transposed ? e % ATT_TILE : e / HD, j = v_transposed ? e / ATT_TILE : e % HD;
+            const int e = tid + i * ATT_THREADS, kk = e / HD, j = e % HD;
             ks[kk][j] = kk < tl ? vv[i] : 0.f;
         }
         __syncthreads();
@@ -521,11 +517,11 @@ size_t sjd_attention_part_elems(const sjd_model *m)
 template <typename T, int HD>
 static int launch_t(const sjd_model *m, sjd_kv *kv, int32_t layer, int32_t rows, int32_t stream, hipStream_t s)
 {
-    const int d = m->cfg.d_model, ms = m->cfg.max_seq, H = m->cfg.n_heads;
+    const int d = m->cfg.d_model, H = m->cfg.n_heads;
     const T *kc = (const T *)(stream ? kv->k_u : kv->k), *vc = (const T *)(stream ? kv->v_u : kv->v);
     SJD_LAUNCH((attn_partial_kernel<T, HD>), dim3(H, kv->att_splits), dim3(ATT_THREADS), 0, s,
                        kv->qact, kc + (size_t)layer * kv->k_layer_stride,
-                       vc + (size_t)layer * kv->v_layer_stride, d, ms, rows, 0, kv->att_splits,
+                       vc + (size_t)layer * kv->v_layer_stride, d, rows, kv->att_splits,
                        kv->att_part, stream, kv->state);
     HIP_TRY(hipGetLastError());
     SJD_LAUNCH((attn_combine_kernel<T, HD>), dim3(H), dim3(256), 0, s, kv->att_part, kv->att_splits, d, rows,

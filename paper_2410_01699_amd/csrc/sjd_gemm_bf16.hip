@@ -70,8 +70,8 @@ __global__ __launch_bounds__(64 * WK) void gemm_fused_kernel(const bf16_t *__res
     // this lane's activation values: token c (+16 mt), columns 32 kt + 8 g .. +8, as two float4, or as
     // 8 bf16 of the hi plane and 8 bytes of the lo plane
     constexpr bool A24 = PRO != SJD_PRO_PLAIN;                                  // operand planes (3 or 4 bytes per value)
-    constexpr bool L16 = PRO == SJD_PRO_NORM16 || PRO == SJD_PRO_A16;           // the lo plane holds bf16 values
-    constexpr bool NORM = PRO == SJD_PRO_NORM || PRO == SJD_PRO_NORM16;
+    constexpr bool L16 = PRO == SJD_PRO_A16;                                    // the lo plane holds bf16 values
+    constexpr bool NORM = PRO == SJD_PRO_NORM;
     const f32x4 *xp = reinterpret_cast<const f32x4 *>(Xv) + lane;
     const uint2 *xl = reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(Xv) + act24_lo_base(KT)) + lane;
     const f32x4 *xp16 = reinterpret_cast<const f32x4 *>(reinterpret_cast<const char *>(Xv) + act24_lo_base(KT)) + lane;
@@ -348,21 +348,23 @@ static int launch_epi(const SjdLinear *lin, const void *act, const float *ssq_in
         dim3 grid(lin->N / (16 * TN)), block(64 * WK);
         const bf16_t *W = (const bf16_t *)lin->w;
 #define GO(EPI) SJD_LAUNCH((gemm_fused_kernel<MT, TN, WK, U, EPI, PRO>), grid, block, 0, s, W, act, ssq_in, eps, lin->N, lin->K, ep)
-        if constexpr (PRO == SJD_PRO_A24 || PRO == SJD_PRO_A16) {
-            // (the plane activations feed the residual projections; the plain store serves the test hook)
+        if constexpr (PRO == SJD_PRO_A24) {
+            // (the plane activations feed the residual projections; the plain store serves the test hooks)
             switch (ep.kind) {
                 case SJD_EPI_STORE: GO(SJD_EPI_STORE); break;
                 case SJD_EPI_RESID: GO(SJD_EPI_RESID); break;
                 default: return SJD_EINVAL;
             }
-        } else {
+        } else if constexpr (PRO == SJD_PRO_NORM) {
             switch (ep.kind) {
                 case SJD_EPI_STORE: GO(SJD_EPI_STORE); break;
-                case SJD_EPI_RESID: GO(SJD_EPI_RESID); break;
                 case SJD_EPI_SILU: GO(SJD_EPI_SILU); break;
                 case SJD_EPI_QKV: GO(SJD_EPI_QKV); break;
                 default: return SJD_EINVAL;
             }
+        } else {
+            if (ep.kind != SJD_EPI_STORE) return SJD_EINVAL;      // (fp32 rows and 2-byte lo planes: test hooks)
+            GO(SJD_EPI_STORE);
         }
 #undef GO
         HIP_TRY(hipGetLastError());
@@ -406,7 +408,7 @@ int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const 
         return sjd_launch_gemm_wide(lin, act, ssq_in, eps, rows, ep, part.sums, part.elems, s);
     }
     if (ep.kind == SJD_EPI_RESID && ep.out24 && (!ep.gain_next || !ep.ssq_out)) return SJD_EINVAL;
-    if (lin->tn < 1 || lin->N % (16 * lin->tn) || lin->K % 32) return SJD_EINVAL;
+    if (lin->tn < 1 || lin->N % (16 * lin->tn) || lin->K % 32 || (lo16 && ssq_in)) return SJD_EINVAL;
     const int mt = rows <= 16 ? 1 : 2;
     const int tn = lin->tn;               // fixed when the weights were packed
     // waves per workgroup: 0 = automatic.  Four waves (longer k-range per wave, more workgroups per CU, one
@@ -427,7 +429,6 @@ int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const 
         if (mt != 1 || wk != 4) return SJD_EINVAL;       // (the only deep variants built)
 #define DEEP(TN)                                                                                      \
         if (tn == TN) {                                                                               \
-            if (lo16 && ssq_in) return launch_epi<1, TN, 4, 4, SJD_PRO_NORM16>(lin, act, ssq_in, eps, ep, s); \
             if (lo16) return launch_epi<1, TN, 4, 4, SJD_PRO_A16>(lin, act, ssq_in, eps, ep, s);      \
             if (ssq_in) return launch_epi<1, TN, 4, 4, SJD_PRO_NORM>(lin, act, ssq_in, eps, ep, s);   \
             if (act24) return launch_epi<1, TN, 4, 4, SJD_PRO_A24>(lin, act, ssq_in, eps, ep, s);     \
@@ -442,14 +443,12 @@ int sjd_launch_gemm_bf16(const SjdLinear *lin, const void *act, int form, const 
     if (mt == MT && tn == TN) {                                                                           \
         if constexpr (MT * TN <= 4) {                                                                     \
             if (wk == 4) {                                                                                \
-                if (lo16 && ssq_in) return launch_epi<MT, TN, 4, 2, SJD_PRO_NORM16>(lin, act, ssq_in, eps, ep, s); \
                 if (lo16) return launch_epi<MT, TN, 4, 2, SJD_PRO_A16>(lin, act, ssq_in, eps, ep, s);         \
                 if (ssq_in) return launch_epi<MT, TN, 4, 2, SJD_PRO_NORM>(lin, act, ssq_in, eps, ep, s);      \
                 if (act24) return launch_epi<MT, TN, 4, 2, SJD_PRO_A24>(lin, act, ssq_in, eps, ep, s);      \
                 return launch_epi<MT, TN, 4, 2, SJD_PRO_PLAIN>(lin, act, ssq_in, eps, ep, s);               \
             }                                                                                             \
         } else if (wk == 4) return SJD_EINVAL;                                                            \
-        if (lo16 && ssq_in) return launch_epi<MT, TN, 8, 2, SJD_PRO_NORM16>(lin, act, ssq_in, eps, ep, s);    \
         if (lo16) return launch_epi<MT, TN, 8, 2, SJD_PRO_A16>(lin, act, ssq_in, eps, ep, s);                 \
         if (ssq_in) return launch_epi<MT, TN, 8, 2, SJD_PRO_NORM>(lin, act, ssq_in, eps, ep, s);              \
         if (act24) return launch_epi<MT, TN, 8, 2, SJD_PRO_A24>(lin, act, ssq_in, eps, ep, s);              \

@@ -1,5 +1,5 @@
-// Pieces shared by the bf16 projection kernels (skinny, span and wide): MFMA operand types, the hi / lo split, and the epilogues that see final fp32 sums (plain
-// store, residual add + operands of the next normalisation, SiLU(gate) * up, RoPE + KV-cache write;
+// Pieces shared by the bf16 projection kernels (skinny, span and wide): MFMA operand types, the hi / lo split, and the epilogues
+// that see final fp32 sums (plain store, residual add + operands of the next normalisation, SiLU(gate) * up, RoPE + KV-cache write;
 // paper Sec. 4.1 Step 2).  Included by those files only.
 #pragma once
 #include "sjd_internal.h"
@@ -8,8 +8,7 @@
 #define SJD_PRO_PLAIN 0     // fp32 activations as they are
 #define SJD_PRO_NORM 1      // planes of x * gain; the token factors rsqrt(mean(x^2) + eps) come from partial sums
 #define SJD_PRO_A24 2       // activations in hi / lo planes, as they are
-#define SJD_PRO_NORM16 3    // as SJD_PRO_NORM, the lo plane in its 2-byte form (the second operand ready made)
-#define SJD_PRO_A16 4       // as SJD_PRO_A24, the lo plane in its 2-byte form
+#define SJD_PRO_A16 3       // as SJD_PRO_A24, the lo plane in its 2-byte form (the second operand ready made; sjd_gemm_bench only)
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -23,23 +22,6 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 &hi, bf16x8 &
         hi[e] = h;
         lo[e] = (__bf16)(x[e] - (float)h);
     }
-}
-
-// second operand of 8 values from their hi plane entry (8 bf16) and their byte plane entry (8 bytes):
-// value = hi bits | lo byte << 8 (as fp32); second operand = bf16(value - hi), exact
-__device__ __forceinline__ bf16x8 lo_from_byte_plane(bf16x8 hi, uint2 lo8)
-{
-    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-    const u32x4 hw = __builtin_bit_cast(u32x4, hi);
-    bf16x8 lo;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const uint32_t hw_ = hw[e >> 1], lw_ = (e < 4) ? lo8.x : lo8.y;
-        const uint32_t hb_ = (e & 1) ? (hw_ & 0xFFFF0000u) : (hw_ << 16);
-        const uint32_t lb_ = ((lw_ >> (8 * (e & 3))) & 0xFFu) << 8;
-        lo[e] = (__bf16)(__uint_as_float(hb_ | lb_) - __uint_as_float(hb_));
-    }
-    return lo;
 }
 
 __device__ __forceinline__ uint32_t pack_hi2(float a, float b, float &ra, float &rb)

@@ -28,7 +28,8 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 
 constexpr int pow2_floor(int x) { int p = 1; while (p * 2 <= x) p *= 2; return p; }
 
-// second operand of 8 values from their hi plane entry and their byte plane entry (as lo_from_byte_plane)
+// second operand of 8 values from their hi plane entry (8 bf16) and their byte plane entry (8 bytes): value = hi bits | lo byte << 8
+// (as fp32); second operand = bf16(value - hi)
 __device__ __forceinline__ bf16x8 lo_by_perm(bf16x8 hi, u32x2_t lo8)
 {
     const u32x4_t hw = __builtin_bit_cast(u32x4_t, hi);
@@ -398,11 +399,14 @@ int sjd_launch_gemm_span(const SjdLinear *lin, const void *act, const float *ssq
     int mt = (rows + 15) / 16;
     if (mt > 4) mt = (mt + 1) & ~1;                       // variants for 16, 32, 48, 64, 96 and 128 rows
 #define CASE(MT, TN, G) if (mt == MT && tn == TN && g == G) return launch_span_t<MT, TN, G>(lin, act, ssq_in, eps, ep, s)
-#define ROWS(TN, G) CASE(1, TN, G); CASE(2, TN, G); CASE(3, TN, G); CASE(4, TN, G); CASE(6, TN, G); CASE(8, TN, G)
-    ROWS(1, 1); ROWS(1, 2); ROWS(1, 3);
-    ROWS(2, 1); ROWS(2, 2); ROWS(2, 3);
-    ROWS(3, 1); ROWS(3, 2);
-#undef ROWS
+#define FEW(TN, G) CASE(1, TN, G); CASE(2, TN, G)        // (what sjd_span_takes lets through up to 32 rows)
+#define MORE(TN, G) CASE(3, TN, G); CASE(4, TN, G); CASE(6, TN, G); CASE(8, TN, G)
+    FEW(2, 2); FEW(2, 3); FEW(3, 2);
+    MORE(1, 1); MORE(1, 2); MORE(1, 3);
+    MORE(2, 1); MORE(2, 2); MORE(2, 3);
+    MORE(3, 1); MORE(3, 2);
+#undef FEW
+#undef MORE
 #undef CASE
     return SJD_EINVAL;
 }

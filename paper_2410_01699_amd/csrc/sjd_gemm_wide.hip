@@ -334,7 +334,7 @@ void sjd_wide_plan(const SjdLinear *lin, int mt, size_t part_elems, int *g_out, 
 size_t sjd_wide_part_elems(const SjdLinear *lin)
 {
     size_t most = 0;
-    for (int mt = 2; mt <= SJD_MTILES; mt += 2) {
+    for (int mt = 4; mt <= SJD_MTILES; mt += 2) {         // (up to 32 rows only sjd_gemm_bench comes here)
         if (sjd_span_takes(lin, mt * 16)) continue;       // (and so all row counts of this variant)
         int g, ks, kps;
         sjd_wide_plan(lin, mt, SIZE_MAX, &g, &ks, &kps);

@@ -226,7 +226,7 @@ struct SjdLinear {
     int32_t u;        // bf16: k-steps per prefetch stage (0 = chosen at launch)
     int32_t wg, wks;  // bf16, wide kernel (more than 32 rows): weight groups per wave, K-slices (0 = chosen at launch)
     int32_t resid;       // bf16: a projection whose output is added to the residual stream (O, down): it may be cut into K-slices
-    int32_t wide_from;   // bf16: rows from which the wide kernel runs (0 = above SJD_ROWS_SKINNY)
+    int32_t wide_from;   // bf16: rows from which the wide kernel runs (0 = above SJD_ROWS_SKINNY; set by sjd_gemm_bench only)
 };
 
 // what the bf16 GEMM does with its final fp32 values
