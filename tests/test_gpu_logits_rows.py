@@ -12,8 +12,8 @@ from paper_2410_01699_amd import synth  # noqa: E402
 
 MARK = -12345.0
 
-# bf16: one and two tiles of the skinny kernel, the wide kernel at each of its row counts, with and without a remainder;
-# 16384 codes at 17..32 rows: the wide kernel's whole-K variant.  fp32: the three row counts of its kernel
+# bf16: one and two tiles of the skinny kernel, the span kernel above 32 rows at the row counts of its variants, with and without a
+# remainder; 16384 codes: the span kernel at any row count.  fp32: rows in one, two and more blocks of 8
 CASES = ([(synth.DTYPE_BF16, 1024, L) for L in (1, 5, 16, 17, 33, 65, 97, 127, 128)] +
          [(synth.DTYPE_BF16, 16384, L) for L in (3, 17, 31, 32, 33)] +
          [(synth.DTYPE_F32, 1024, L) for L in (1, 5, 8, 9, 17, 32)])
