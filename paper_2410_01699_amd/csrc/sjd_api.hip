@@ -234,7 +234,7 @@ extern "C" int sjd_kv_create(const sjd_model *m, sjd_kv **out)
     A(kv->x24, c.dtype == 1 ? act24_bytes((int)d / 32) : 16);
     A(kv->ssq, c.dtype == 1 ? R * ssq_stride((int)d) * 4 : 16);
     A(kv->h, c.dtype == 0 ? R * d * 4 : 16);
-    // fp32 models: the output of a linear layer; bf16 models: the fp32 sums of the wide projection kernel's
+    // fp32 models: the output of a linear layer; bf16 models: the fp32 sums of the wide and the sliced projections'
     // K-slices, as many of them as any linear layer is cut into at any row count
     if (c.dtype == 1) {
         kv->part_elems = 0;

@@ -213,7 +213,8 @@ __device__ __forceinline__ void arrive_and_wait()
 //    and non-temporal ones, us a forward: 7B, eight images of 16 drafts at 1239 positions (10 GB) 7204 and 6888, at 583
 //    6262 and 6192, one at 583 (0.6 GB) 2756 and 2736.  Smaller caches are still there when the next forward reads them, and when
 //    the QKV epilogue writes into their lines, unless they were read so: 775M, one image at 633 positions (0.19 GB) 773 and 789, eight
-//    at 200 1628 and 1649, 7B at 100 (0.1 GB) 2632 and 2648.  Two query groups, 775M window of 64 at 1100 positions 1190 and 1215;
+//    at 200 1628 and 1649, 7B at 100 (0.1 GB) 2632 and 2648; 775M whole images 1948 and 1924 tokens/s.  (Forwards that take turns between
+//    caches keep none of them: 775M at 633 positions 803 and 798.)  Two query groups, 775M window of 64 at 1100 positions 1190 and 1215;
 //  - loads in the order of their use (Q, K, V; the next block's K during the probabilities), as global accesses with
 //    nothing conditional between a load and its use, so that each wait is for its own loads only; and the arguments of the
 //    first loads in registers (16 queries at 600 positions: 8.3 -> 6.7 us; 7B forward of 16 drafts there 2998 -> 2942).

@@ -13,11 +13,11 @@
 //  - up to eight row tiles.  A wave's activation tiles are refilled in place as soon as their products are issued, the
 //    weights of the next k-step are requested one k-step ahead.
 //
-// What bounds it, 7B gate/up (180 MB) alone on cold weights: up to 32 rows the weight stream (16 rows 29.8 us, 32 rows 31.5;
-// a kernel that only reads these bytes from as many workgroups 28; the skinny kernel was at 31.2 and 40.3).  Above, the
-// activations, which every workgroup reads from L2 in between (64 rows 38.6 us, 128 rows 57; without them 33 and 36, without
-// the products 36.5 and 48): loads return in order, so tiles that hit L2 wait for weights that do not.  The wide kernel and its
-// second kernel need 46 and 62-65 us.  Inside a forward, per launch: 29.2 us at 16 rows (skinny 32.2), 31.0 at 32 (the wide
+// What bounds it, 7B gate/up (180 MB) alone on cold weights: up to 32 rows the weight stream (16 rows 29.7 us, 32 rows 31.5;
+// a kernel that only reads these bytes 26 to 32; the skinny kernel was at 32.3 and 39.2).  Above, the activation loads in between,
+// 64 rows 38.5 us, 128 rows 56.4: without these loads 32.9 and 45.5, but 33.8 and 53.9 with loads of no bytes in their place, so at 128 rows
+// it is less the bytes from L2 than the loads themselves (they return in order, behind weights from HBM) and the products (without them
+// 34.7 and 50.0).  QKV at 128 rows 38.0: 25.5, 34.8 and 35.4.  The wide kernel and its second kernel need 42.5 and 62.7 us.  Inside a forward, per launch: 29.2 us at 16 rows (skinny 32.2), 31.0 at 32 (the wide
 // kernel with final sums in it 38.5), 37.6 at 64 (wide 40.7 + 5.3), 58.7 at 128 (wide 55.8 + 9.5).
 #include "sjd_gemm_epi.h"
 

@@ -1,7 +1,7 @@
 // bf16 projections of a window forward with MORE than 32 rows (paper Sec. 4.1 Step 2 for windows of 64
 // tokens, for guided windows of 32 -- two contexts -- and for batches of images that share one pass
-// over the weights): C[M x N] = A[M x K] * W^T, M = 33 .. 128, for the shapes that the span kernel does not take
-// (few features for their reduction: O, down and the LM head of the 7B model); also its down projection from 17 rows on.
+// over the weights): C[M x N] = A[M x K] * W^T, M = 33 .. 128, for the shapes and rows that the span kernel does not take, whole
+// or in slices (of the 7B model down above 32 rows, the LM head above 48, O above 64; of wider models QKV and gate/up too).
 //
 // With this many rows a workgroup can no longer afford a private copy of the activations per wave (M
 // rows cost M * 96 bytes of activations per KiB of weights), so the roles inside a workgroup change
@@ -17,8 +17,8 @@
 //    writes its fp32 sums as whole accumulator fragments, and a second kernel adds the K-slices in
 //    slice order (deterministic), applies the token factors of a folded RMSNorm and runs the same
 //    epilogues as the skinny kernel (residual, SiLU * up, RoPE + cache write, plain store).  (Adding the
-//    slices in the last workgroup to arrive instead was measured 3x slower: the device-scope fences around
-//    its arrival counter write back and invalidate the L2 of the XCD.)
+//    slices in the last workgroup to arrive behind device-scope fences was measured 3x slower: they write back and
+//    invalidate the L2 of the XCD.  The sliced spans do it without a fence, where few slices of few rows meet.)
 // At M = 128 the two MFMAs per weight tile and M-tile price the matrix cores at about 9.8 TB/s of
 // weights; measured, the kernel runs at about 30 % of the bf16 MFMA peak there: the one regime of this path where
 // matrix-core utilisation is a meaningful number.  What bounds it is known in part only: at 128 rows the CUs fill their
@@ -265,11 +265,10 @@ int sjd_gemm_wide_setup()
 // groups the K-slices of a group and its epilogue share an L2, so the count is rounded up (the added workgroups return
 // at once) where all workgroups of the first kernel are resident together, one per CU, and there are 32 groups or more.
 // Both kernels together, alone on cold weights, not rounded and rounded:
-//   775M QKV, 36 groups x 6 slices: 10.8 -> 9.8 us at 64 rows, 12.5 -> 11.0 at 96, 14.8 -> 13.1 at 128
-//   7B gate/up up to 64 rows, 86 x 2: 42.9 -> 41.0 in one run, 46.1 -> 45.7 in another; at 128 rows, 172 x 4 and so not
-//   resident together: 61.6 -> 68.5, a forward of 8 x 16 rows 6650 -> 6891
-//   775M O and down, 12 groups: alone 8.5 -> 8.0 and 11.1 -> 10.5, but a forward of 4 x 16 rows 1512 -> 1532 and a prompt
-//   of 121 1871 -> 1907 (rounded to 16, four XCDs have two groups and four have one)
+//   12848 x 640, 101 groups x 2 slices: 12.4 -> 10.6 us at 64 rows, 18.9 -> 14.5 at 128
+//   30784 x 2048, 121 x 2: 33.7 -> 32.4 at 64 rows; 29504 x 4096, 116 x 2: 49.5 -> 48.5; 25664 x 512, 201 x 2: not resident, as before
+//   few groups, 12 of them (O and down of 775M when they ran here): alone 8.5 -> 8.0 and 11.1 -> 10.5, but forwards 1.3 and 1.9 %
+//   slower (rounded to 16, four XCDs have two groups and four have one)
 static int wide_cols(int groups, int g, int ks)
 {
     const int cols = (groups + WIDE_WAVES * g - 1) / (WIDE_WAVES * g), up = (cols + 7) & ~7;

@@ -377,11 +377,11 @@ int sjd_launch_gemm_sliced(const SjdLinear *lin, const void *act, int32_t rows, 
 int sjd_repack_bf16(const bf16_t *src_dev, bf16_t *dst_dev, int32_t N, int32_t K, int32_t tn, int32_t perm, int32_t d,
                     int32_t hd, hipStream_t s);
 void sjd_choose_tiles(SjdLinear *lin);
-// bf16 projection: act = the 3-byte planes described at act24_idx() (act24 set) or fp32 [SJD_ROWS_MAX x K]
+// bf16 projection: act = the planes described at act24_idx(), in the form that sjd_gemm_form names, or fp32 [SJD_ROWS_MAX x K]
 // in act_off order.  ssq_in != NULL (planes only): the planes hold x * gain and ssq_in the partial sums
 // of squares of x ([rows][ssq_stride(K)]); the projection applies rsqrt(mean(x^2) + eps) per row.
-// More than SJD_ROWS_SKINNY rows go to the wide kernel (planes only), which needs `part`: room for the fp32
-// sums of its K-slices (part_elems floats, at least 16 * ceil(rows / 16) * N); NULL = skinny kernel only.
+// The wide and the sliced kernel need `part`: room for the fp32 sums of their K-slices (sjd_wide_part_elems and sjd_sliced_elems
+// floats; with less the wide kernel cuts fewer slices, down to one of 32 * ceil(rows / 32) * N) and, sliced, the counters.
 #define SJD_ACT_F32 0     // fp32 values in act_off order (test hook)
 #define SJD_ACT_P3 1      // operand planes, 1-byte lo plane (3 bytes per value)
 #define SJD_ACT_P4 2      // operand planes, 2-byte lo plane (4 bytes per value)

@@ -31,8 +31,8 @@ def test_wide_column_groups_run_there(B, M, N, K, plan):        # noqa: F811
 
 
 # Precision of a whole output against 64 bits: the 7B QKV and gate/up projections above 96 rows, which split K over the waves of a
-# workgroup.  Four chains of 32 k-steps each are 2.80e-7 (2-norm) away, whatever the rows and the seed; fewer are longer chains of
-# fp32 sums: 3.24e-7 for three, 3.97e-7 for two.
+# workgroup.  Eight chains of 16 k-steps (QKV) are 2.02e-7 (2-norm) away, four of 32 (gate/up) 2.80e-7, whatever the rows and the seed;
+# fewer are longer chains of fp32 sums: 3.24e-7 for three, 3.97e-7 for two.
 @pytest.mark.parametrize("M", [97, 128])
 @pytest.mark.parametrize("N", [12288, 22016])
 def test_sliced_projection_precision(B, M, N):        # noqa: F811
