@@ -380,12 +380,17 @@ size_t sjd_sliced_elems(const SjdLinear *lin)
 //    8192 logits) of 64, 96 and 128 rows had become 449, 570 and 701 us, 437, 531 and 626 before
 // Two-tile groups at 17 to 32 rows are the exception: 32768 x 4096 53.3 and 55.2, x 7168 100.8 and 94.7, 57344 x 8192 187.7 and 172.3.
 // Nor above 64 rows of 8192 features and more (2.4 MB of activations for every workgroup at 96 rows): 24576 x 8192 alone 72.3 and 73.1 us at 64 rows, 79.7 and 86.5 at 96, 95.5 and 101.1 at 128; 16384 x 8192 at 128 73.6 and 86.6; 21504 x 7168 97.1 and 86.4.
+// Nor, above 96 rows, four tiles a workgroup with 3072 features and more: their 32 fragments leave four waves a workgroup, for two thirds of
+// the weights that six tiles give it.  Forwards of two layers at 128 rows, wide kernel and span: d = 3072 (gate/up) 289 and 294 us, with 16384
+// logits 301 and 310; d = 4096 with 16384 logits 399 and 406; d = 5120 (QKV) 592 and 600.  At 80 and 96 rows (eight waves) the
+// span kernel is up to 3 % of such a forward ahead; alone 16384 x 2048 at 128 rows 30.4 and 25.6.
 bool sjd_span_takes(const SjdLinear *lin, int32_t rows)
 {
     const int groups = lin->N / 16 / lin->tn, g = sjd_span_groups(lin), tiles = g * lin->tn;
     const bool one_round = (groups + g - 1) / g <= 256;
     if (lin->K > SPAN_K_MAX) return false;
     if (rows <= SJD_ROWS_SKINNY) return groups >= 512 && tiles >= 4 && (one_round || (rows > 16 && lin->tn == 2));
+    if (rows > 96 && tiles == 4 && lin->K >= 3072) return false;
     const int64_t act = (int64_t)((rows + 15) / 16 * 16) * lin->K * 3;
     return one_round && (rows <= 64 || lin->K < 8192) && (tiles >= 3 || act <= 600 * 1024);
 }

@@ -39,6 +39,10 @@ def test_spans_are_one_round(M):
         for K in (512, 4096, 8192):
             kernel, tn, g, ks = B.sjd_gemm_plan(M, tiles * 16, K)
             assert kernel != "span" or -(-tiles // tn // g) <= 256 or (16 < M <= 32 and tn == 2)
+    # four tiles a workgroup above 96 rows: four waves only (gate/up of d = 3072, QKV of d = 5120, 16384 logits of d = 4096)
+    for N, K in ((16384, 3072), (15360, 5120), (16384, 4096)):
+        assert (B.sjd_gemm_plan(M, N, K)[0] == "span") == (32 < M <= 96 or (M <= 32 and N == 16384)), (M, N, K)
+    assert B.sjd_gemm_plan(M, 16384, 2048)[0] == "span"
     # long reductions above 64 rows
     assert B.sjd_gemm_plan(M, 24576, 8192)[0] == ("wide" if M > 64 else "span")
     # what fills the chip in one round stays: 7B QKV and gate/up above 32 rows, gate/up at any row count
