@@ -351,7 +351,7 @@ def main():
              and args.init_mode < 0 and not args.no_refine and not args.no_graph)
     # (the counter runs were made on the default configuration of a workload only)
     traffic, traffic_src = recorded_traffic(args.workload) if plain else (None, None)
-    roofline = {"bound": "hbm", "kernel": "gemm_fused_kernel (all projections + LM head)" if shape.dtype == 1
+    roofline = {"bound": "hbm", "kernel": "gemm_span_kernel, gemm_fused_kernel and gemm_wide_kernel (all projections + LM head)" if shape.dtype == 1
                 else "gemm_f32_kernel", "achieved": g["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": g["GBps"] / HBM_PEAK_GBS, "traffic": traffic,
                 "traffic_source": None if traffic is None else f"recorded rocprofv3 --pmc run, {traffic_src} (not measured by this run)",
